@@ -171,8 +171,9 @@ def prepare(case, seed):
             s.f.ls_ffn_set_layer(l, SimpleNamespace(
                 **{n: _host(getattr(w, n)) for n in ("gate", "up", "down", "bias", "p1", "p2")},
                 threshold=SWIGLU_T if c["act"] == "swiglu" else 0.0))
-    if c.get("zero_skip"):
+    if c.get("zero_skip"):  # applies to the per-kernel path
         s.f.ls_configure(lsffn.LS_CFG_ZERO_SKIP, 1)
+        s.f.ls_configure(lsffn.LS_CFG_DECODE_PATH, 1)
     dev = s.x0.device
     s.x = torch.empty_like(s.x0)
     s.scores = torch.empty((B, nb), device=dev)
