@@ -61,6 +61,8 @@ inline int predictor_folds(int d, int r, int n_blk, ls_dtype t) {
     return 4.0 * n_blk * d <= (double)elem_size(t) * ((double)r * d + (double)n_blk * r) ? 1 : 0;
 }
 
+int cu_count();  // compute units of the current device (0 when unknown)
+
 // ---- kernel launchers (ls_kernels.hip) -------------------------------------------------
 // The MLP input h = x / sqrt(mean(x^2) + 1e-6) is never materialised: a kernel that reads x
 // for a dot product also sums x^2 and scales the dot product (h.w = scale * (x.w)).

@@ -585,7 +585,7 @@ hipError_t launch_select(const float* scores, int B, int n_blk, int mode, int k,
 }
 
 // compute units of the current device (0 when unknown), queried once per device
-static int cu_count() {
+int cu_count() {
     static std::atomic<int> cached[64];
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;

@@ -4,14 +4,15 @@
 // 16 neurons, [16 x d] weight rows times [d x B] activations.  These kernels run them as
 // v_mfma_f32_16x16x32_{f16,bf16}: the weights are the A operand, loaded straight from
 // their rows (one 16-byte load per lane per step), and the activations are the B operand,
-// padded with zeros to 16 token columns.  Activations are fp32, so each one is split into
-// a 16-bit "hi" part and the 16-bit rounding of the remainder ("lo"); W.hi + W.lo carries
-// about 22 (f16) or 16 (bf16) significant bits of the activation, with fp32
-// accumulation in the matrix cores.  Results match the VALU kernels to fp32 rounding
-// (Eq. 1 of the paper, union over tokens as for the VALU path).
+// token columns.  Activations are fp32, so each one enters as the sum of 16-bit parts (a "hi"
+// part and the 16-bit rounding of the remainder, "lo"; in the resident gate/up kernel a third
+// part for bfloat16), with fp32 accumulation in the matrix cores.  Results match the VALU
+// kernels to fp32 rounding (Eq. 1 of the paper, union over tokens as for the VALU path).
 //
 // Lane layout of v_mfma_f32_16x16x32 (lane l, i < 8 / i < 4):
 //   A[l % 16][8 (l / 16) + i],  B[8 (l / 16) + i][l % 16],  C[4 (l / 16) + i][l % 16].
+#include <algorithm>
+
 #include "ls_device.h"
 #include "ls_internal.h"
 
@@ -81,9 +82,315 @@ __device__ inline int list_end_m(const int32_t* count, int end, int n_blk) {
     return end < c ? end : c;
 }
 
+// 16 bytes of the input at a wave-uniform base plus a per-lane byte offset
+__device__ __forceinline__ f32x4 gload_x(const float* uniform_base, uint32_t byte_off) {
+    typedef const __attribute__((address_space(1))) f32x4* gf4_ptr;
+    const uint64_t b = (uint64_t)uniform_base;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    return *(gf4_ptr)((const char*)(((uint64_t)hi << 32) | lo) + byte_off);
+}
+
+// a barrier that orders LDS only: global loads already issued stay in flight
+__device__ __forceinline__ void lds_barrier_m() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// ---- gate/up, inputs in registers -------------------------------------------------------------------------
+// The inputs stay in registers.  A workgroup owns many groups of 8 neurons; its W waves cut the
+// d values of a row into W slices of NK (or fewer) steps of 64, and a wave keeps its slice of
+// every token, already split into 16-bit parts, in registers for the whole launch, so a compute
+// unit reads x once instead of once per 16 rows.  The per-CU memory path is what bounds a
+// batched gather (about 7 TB/s over the chip whatever the bytes are): read again for every
+// group, x cost 8 d bytes per token beside 64 d bytes of weights.
+//
+// The weights go from global memory straight into MFMA operands: one load instruction covers 8
+// rows x 128 bytes (whole cache lines).  Lane l holds row l % 8, chunk l / 8 of 8 values, so as
+// operand A its row index l % 16 means (half h = (l / 8) % 2, row l % 8) and holds the 8 values
+// of chunk 2 (l / 16) + h.  Operand B is laid out the same way: column (h, slot).  Of the 16 x 16
+// products the two diagonal 8 x 8 blocks (equal halves) are the row's even and odd chunks; the
+// rest is not used.  A streaming read in this pattern measured 5.75 TB/s (8 KB rows, 180 MB)
+// against 5.99 for 1 KB of one row per instruction, which would need a transpose through LDS,
+// and 4.3 - 5.1 for 16 rows x 64 bytes, the plain operand layout.
+//
+// The 8 slots of a fragment hold P parts x BP tokens (BP: tokens padded to 2, 4 or 8); with more
+// than 8 there are NF fragments.  A part is the 16-bit rounding of what the parts before it left,
+// so P = 2 float16 parts carry 22 bits of an fp32 value and P = 3 bfloat16 parts all 24.  float16
+// parts: the slice is scaled by a power of two to at most 1 in magnitude and the second part by
+// 2^11, so that neither overflows nor goes subnormal; both factors are taken out of the sums.
+//
+// Measured against the staged kernel below (which keeps rows longer than the registers hold):
+// Mistral-7B shape at B = 4 (105 blocks, 220 MB) 61.7 -> 41.6 us, 13B shape at B = 8 (138
+// blocks, 181 MB) 45.0 -> 37.2 us.  From 45 to 180 MB it reads 7.0 TB/s; about 8 us of a launch
+// are the list, the input's conversion and the last sums.
+constexpr int kGuWaves = 8;   // slices, at most
+
+// Parts of values, two at a time (a word holds the pair's 16-bit parts).  first(): the leading
+// part; v is left as the (scaled) remainder; a value that is not finite leaves none.
+template <ls_dtype T>
+struct Part;
+template <>
+struct Part<LS_F16> {
+    static constexpr int kParts = 2;
+    static constexpr int kShift = 11;  // the second part is scaled by 2^11
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    __device__ static inline uint32_t pack(float a, float b) {
+        const f16x2 h = {(_Float16)a, (_Float16)b};
+        return __builtin_bit_cast(uint32_t, h);
+    }
+    __device__ static inline float rest(float v) {
+        const float r = (v - (float)(_Float16)v) * 2048.f;
+        return fabsf(v) < INFINITY ? r : 0.f;
+    }
+};
+template <>
+struct Part<LS_BF16> {
+    static constexpr int kParts = 3;   // 8 bits each, cut off: exact
+    static constexpr int kShift = 0;
+    // the upper halves of two values (a NaN stays one: its quiet bit is set)
+    __device__ static inline uint32_t pack(float a, float b) {
+        const uint32_t ua = __float_as_uint(a) | (a != a ? 0x400000u : 0u);
+        const uint32_t ub = __float_as_uint(b) | (b != b ? 0x400000u : 0u);
+        return (ua >> 16) | (ub & 0xffff0000u);
+    }
+    __device__ static inline float rest(float v) {
+        const float r = v - __uint_as_float(__float_as_uint(v) & 0xffff0000u);
+        return fabsf(v) < INFINITY ? r : 0.f;
+    }
+};
+
+// FULL: every wave has NK steps (d / 64 = W NK); the addresses of a unit's loads then differ only in
+// their immediate offsets.
+template <ls_dtype T, int NK, int BP, bool FULL>
+__global__ __launch_bounds__(64 * kGuWaves) void gateup_mfma_kernel(
+    const uint8_t* __restrict__ blocks, size_t block_bytes, const int32_t* __restrict__ slot_table,
+    const void* __restrict__ bias, float thresh, const float* __restrict__ x, int B, int d, int blk,
+    int n_blk, int F, const int32_t* __restrict__ idx, const int32_t* __restrict__ count, int begin,
+    int end, float* __restrict__ a_buf, int reglu, int rms) {
+    using S = Split<T>;
+    typedef typename S::vec vec;
+    constexpr int P = Part<T>::kParts;
+    constexpr int NF = (P * BP + 7) / 8;
+    // loads of a unit: one row set's steps, or half of them where two whole ones and the
+    // fragments would not fit the 256 registers
+    constexpr int UL = NK <= 8 || 8 * NK + 4 * NF * NK <= 160 ? NK : NK / 2;
+    constexpr int UM = NK / UL;                // units per row set (gate, up)
+    static_assert(NK % UL == 0, "whole units");
+    // partial sums of two groups: [wave][gate, up][fragment][half][slot][row]
+    __shared__ __attribute__((aligned(16))) float part[2][kGuWaves][2][NF][2][8][8];
+    __shared__ float pss[kGuWaves][8];
+    const int W = (int)(blockDim.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int gpe = blk / 8;  // groups per entry
+    // this wave's steps [s0, s0 + nst) of the row's d / 64
+    const int steps = d / 64;
+    const int s0 = FULL ? NK * wave : steps * wave / W, nst = FULL ? NK : steps * (wave + 1) / W - s0;
+    const size_t row_bytes = (size_t)d * 2;
+    const uint32_t lane_off = (uint32_t)(lane & 7) * (uint32_t)row_bytes + (uint32_t)(lane >> 3) * 16u;
+
+    // x, this wave's slice of the lane's token, requested before the list is read.  Every address
+    // is in bounds: a token past the batch reads token 0 (its columns are never used), a step
+    // past the slice its first
+    const int tok = (lane & 7) & (BP - 1);
+    const int half = (lane >> 3) & 1;
+    f32x4 xv[NK][2];
+    {
+        const uint32_t xo = ((uint32_t)(tok < B ? tok : 0) * (uint32_t)d + 16u * (uint32_t)(lane >> 4) + 8u * (uint32_t)half) * 4u;
+        const float* xs = x + (size_t)s0 * 64;
+#pragma unroll
+        for (int s = 0; s < NK; ++s) {
+            const uint32_t o = xo + (uint32_t)(s < nst ? s : 0) * 256u;
+            xv[s][0] = gload_x(xs, o);
+            xv[s][1] = gload_x(xs, o + 16u);
+        }
+    }
+    const int n_groups = (list_end_m(count, end, n_blk) - begin) * gpe;
+    if ((int)blockIdx.x >= n_groups) return;
+
+    // a group's first gate row in this wave's slice (an invalid or absent block reads block 0,
+    // whose products are dropped at the end)
+    auto slot_of = [&](int b) { return b < 0 || b >= n_blk ? -1 : (slot_table ? slot_table[b] : b); };
+    auto group_base = [&](int slot, int gi) {
+        return blocks + (size_t)(slot < 0 ? 0 : slot) * block_bytes + (size_t)(gi % gpe) * 8 * row_bytes +
+               (size_t)s0 * 128;
+    };
+    u32x4 buf[2][UL];
+    auto load_unit = [&](u32x4 (&u4)[UL], const uint8_t* base, int u) {
+        const uint8_t* rows = base + (u / UM ? (size_t)blk * row_bytes : 0);
+#pragma unroll
+        for (int i = 0; i < UL; ++i) {
+            const int s = (u % UM) * UL + i;  // steps past the slice repeat its first one
+            u4[i] = gload_u(rows, lane_off + (uint32_t)(s < nst ? s : 0) * 128u);
+        }
+    };
+    int gi = (int)blockIdx.x;
+    int b_cur = idx[begin + gi / gpe];
+    const int gi2 = gi + (int)gridDim.x;
+    int b_nxt = gi2 < n_groups ? idx[begin + gi2 / gpe] : -1;
+    int slot = slot_of(b_cur);
+    const uint8_t* base = group_base(slot, gi);
+    load_unit(buf[0], base, 0);
+    load_unit(buf[1], base, 1);
+
+    // x into parts
+    vec xf[NF][NK];
+    float unscale = 1.f;
+    {
+        float ss = 0.f, mx = 0.f;
+#pragma unroll
+        for (int s = 0; s < NK; ++s)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float v = s < nst ? xv[s][i >> 2][i & 3] : 0.f;
+                xv[s][i >> 2][i & 3] = v;
+                ss = fmaf(v, v, ss);
+                if (T == LS_F16 && fabsf(v) < INFINITY) mx = fmaxf(mx, fabsf(v));
+            }
+        // lanes l, l + 8, l + 16, ... hold the same slot
+#pragma unroll
+        for (int off = 8; off < 64; off <<= 1) {
+            ss += __shfl_xor(ss, off, 64);
+            if (T == LS_F16) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+        }
+        if (lane < 8) pss[wave][lane] = ss;
+        int ex = 0;
+        if (T == LS_F16 && mx > 0.f) {
+            ex = (int)((__float_as_uint(mx) >> 23) & 0xffu) - 127;  // a subnormal maximum: -127
+            unscale = ldexpf(1.f, ex);
+        }
+#pragma unroll
+        for (int s = 0; s < NK; ++s) {
+            u32x4 words[NF];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float v0 = xv[s][j >> 1][(2 * j) & 3], v1 = xv[s][j >> 1][(2 * j + 1) & 3];
+                if (T == LS_F16) v0 = ldexpf(v0, -ex), v1 = ldexpf(v1, -ex);
+                // slot q of fragment f is part (8 f + q) / BP
+                float p0[P], p1[P];
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    p0[p] = v0;
+                    p1[p] = v1;
+                    if (p + 1 < P) v0 = Part<T>::rest(v0), v1 = Part<T>::rest(v1);
+                }
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    float a = p0[f * 8 / BP], b = p1[f * 8 / BP];
+#pragma unroll
+                    for (int p = f * 8 / BP + 1; p < P && p * BP < f * 8 + 8; ++p) {
+                        const bool mine = (lane & 7) >= p * BP - f * 8;
+                        a = mine ? p0[p] : a;
+                        b = mine ? p1[p] : b;
+                    }
+                    words[f][j] = Part<T>::pack(a, b);
+                }
+            }
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                asm volatile("" : "+v"(words[f]));
+                xf[f][s] = S::from_raw(words[f]);
+            }
+            // one step at a time: its inputs' registers become its fragments'
+            if (s + 1 < NK) asm volatile("" : "+v"(xv[s + 1][0]), "+v"(xv[s + 1][1]));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    lds_barrier_m();
+    // the finishing threads' token and its RMS scale
+    const int ft = lane >> 3, fr = lane & 7;
+    float sc = 1.f;
+    if (rms) {
+        float q = 0.f;
+        for (int w = 0; w < W; ++w) q += pss[w][ft & (BP - 1)];
+        sc = rms_scale(q, d);
+    }
+
+    for (int it = 0;; ++it) {
+        const int gn = gi + (int)gridDim.x;
+        const bool more = gn < n_groups;
+        const int slot_n = slot_of(b_nxt);
+        const uint8_t* base_n = group_base(slot_n, gn);
+        const int b_this = b_cur;
+        {
+            const int g2 = gn + (int)gridDim.x;
+            b_cur = b_nxt;
+            b_nxt = g2 < n_groups ? idx[begin + g2 / gpe] : -1;
+        }
+        f32x4v c[2][NF];
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int f = 0; f < NF; ++f) c[m][f] = f32x4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < 2 * UM; ++u) {
+#pragma unroll
+            for (int i = 0; i < UL; ++i) {
+                const int s = (u % UM) * UL + i;
+                u32x4 raw = buf[u & 1][i];
+                if (s >= nst) raw = u32x4{0u, 0u, 0u, 0u};
+                const vec a = S::from_raw(raw);
+#pragma unroll
+                for (int f = 0; f < NF; ++f) c[u / UM][f] = S::mfma(a, xf[f][s], c[u / UM][f]);
+            }
+            if (u + 2 < 2 * UM) load_unit(buf[u & 1], base, u + 2);
+            else if (more) load_unit(buf[u & 1], base_n, u + 2 - 2 * UM);
+        }
+        // lane l: rows 4 (l / 16) + i of column l % 16; rows and columns of the same half count
+        if ((lane >> 5) == half) {
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    f32x4v v = c[m][f];
+                    if (T == LS_F16) {
+                        const float k = ldexpf(unscale, -Part<T>::kShift * ((f * 8 + (lane & 7)) / BP));
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[i] *= k;
+                    }
+                    *reinterpret_cast<f32x4v*>(&part[it & 1][wave][m][f][half][lane & 7][4 * ((lane >> 4) & 1)]) = v;
+                }
+        }
+        // one barrier a group: a buffer is written again two groups later, past the next barrier,
+        // which the finishing wave joins after its reads
+        lds_barrier_m();
+        if (wave == it % W && ft < B) {
+            float g = 0.f, uv = 0.f;
+            for (int w = 0; w < W; ++w)
+#pragma unroll
+                for (int p = P - 1; p >= 0; --p) {
+                    const int q = p * BP + (ft & (BP - 1));
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        g += part[it & 1][w][0][q >> 3][h][q & 7][fr];
+                        uv += part[it & 1][w][1][q >> 3][h][q & 7][fr];
+                    }
+                }
+            const int e = begin + gi / gpe, r0 = (gi % gpe) * 8;
+            float a = 0.f;
+            if (slot >= 0) {
+                g = sc * g + (bias ? Wt<T>::scalar(bias, (size_t)b_this * blk + r0 + fr) : 0.f);
+                uv = sc * uv;
+                if (reglu) {
+                    a = fmaxf(g, 0.f) * uv;
+                } else {
+                    const float sg = g / (1.f + expf(-g));
+                    a = fabsf(sg) > thresh ? sg * uv : 0.f;
+                }
+            }
+            a_buf[(size_t)ft * F + (size_t)e * blk + r0 + fr] = a;
+        }
+        if (!more) break;
+        gi = gn;
+        base = base_n;
+        slot = slot_n;
+    }
+}
+
+// ---- gate/up, any d ---------------------------------------------------------------------------------
 constexpr int kWaves = 4;     // gate/up: waves per workgroup
 constexpr int kRowsW = 32 / kWaves;  // gate/up: staged rows loaded by each wave per chunk
-constexpr int kUnroll = 8;    // gate/up: K steps in flight per wave
 constexpr int kUnrollDn = 4;  // down: (entry, K step) items in flight per wave, at most
 constexpr int kWavesDn = 16;  // down: waves per workgroup (one 16-column tile)
 
@@ -102,7 +409,7 @@ constexpr int kRowPitch = 2 * kChunkK + 16;  // LDS bytes per staged row
 // three waves per SIMD (at most 168 registers a lane): three workgroups per CU
 constexpr int kGuWavesPerEu = 3;
 template <ls_dtype T, ls_act A, bool RMS>
-__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(kGuWavesPerEu))) void gateup_mfma_kernel(
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(kGuWavesPerEu))) void gateup_staged_kernel(
     const uint8_t* __restrict__ blocks, size_t block_bytes, const int32_t* __restrict__ slot_table,
     const void* __restrict__ bias, float thresh, const float* __restrict__ h, int B, int d, int blk,
     int n_blk, int F, const int32_t* __restrict__ idx, const int32_t* __restrict__ count, int begin,
@@ -366,22 +673,72 @@ bool mfma_path(const Shape& s, int B) {
     return B >= kMfmaMinBatch && B <= 16 && s.dtype != LS_F32 && s.blk % 32 == 0 && s.d % 32 == 0;
 }
 
+template <ls_dtype T, int BP>
+static hipError_t gateup_resident_bp(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* x, int B,
+                                     const int32_t* idx, const int32_t* count, int begin, int end, float* a_buf,
+                                     hipStream_t st) {
+    const size_t bb = s.block_elems * elem_size(s.dtype);
+    const int steps = s.d / 64;
+    const long groups = (long)(end - begin) * (s.blk / 8);
+    const int cus = std::max(1, cu_count());
+#define LS_GUR_K(NK, FULL)                                                                                             \
+    hipLaunchKernelGGL((gateup_mfma_kernel<T, NK, BP, FULL>), dim3((unsigned)grid), dim3(64 * W), 0, st, L.blocks,  \
+                       bb, slot_table, L.bias, L.threshold, x, B, s.d, s.blk, s.n_blk, s.F, idx, count, begin, end,    \
+                       a_buf, s.act == LS_ACT_REGLU ? 1 : 0, s.prenorm)
+#define LS_GUR(NK)                                                                                                     \
+    do {                                                                                                               \
+        const int W = (steps + NK - 1) / NK;                                                                           \
+        const long grid = std::min<long>(groups, (long)cus * std::max(1, kGuWaves / W));                               \
+        if (steps == W * NK) LS_GUR_K(NK, true); else LS_GUR_K(NK, false);                                             \
+    } while (0)
+    // the shortest slice that eight waves or fewer cover the row with
+    if (steps <= 4 * kGuWaves) LS_GUR(4);
+    else if (steps <= 6 * kGuWaves) LS_GUR(6);
+    else if (steps <= 8 * kGuWaves) LS_GUR(8);
+    else if (steps <= 10 * kGuWaves) LS_GUR(10);
+    else if (steps <= 12 * kGuWaves) LS_GUR(12);
+    else if (steps <= 16 * kGuWaves) LS_GUR(16);
+    else return hipErrorInvalidValue;
+#undef LS_GUR
+#undef LS_GUR_K
+    return hipGetLastError();
+}
+
+template <ls_dtype T>
+static hipError_t gateup_resident_t(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* x, int B,
+                                    const int32_t* idx, const int32_t* count, int begin, int end, float* a_buf,
+                                    hipStream_t st) {
+    if (B <= 4) return gateup_resident_bp<T, 4>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, st);
+    return gateup_resident_bp<T, 8>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, st);
+}
+
+// The resident kernel's registers hold up to 16 steps of 64 values a wave beside the loads in
+// flight, but only 12 where the parts take three fragments (bfloat16, 5 to 8 tokens).
+static bool resident_ok(const Shape& s, int B) {
+    const int nk = s.dtype == LS_BF16 && B > 4 ? 12 : 16;
+    return s.d <= 64 * nk * kGuWaves;
+}
+
 hipError_t launch_gateup_mfma(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                               const float* x, int B, const int32_t* idx, const int32_t* count,
                               int begin, int end, float* a_buf, hipStream_t st) {
+    if (end <= begin) return hipSuccess;
+    if (resident_ok(s, B)) {
+        return s.dtype == LS_F16 ? gateup_resident_t<LS_F16>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, st)
+                                 : gateup_resident_t<LS_BF16>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, st);
+    }
     const long groups = (long)(end - begin) * (s.blk / 16);
-    if (groups <= 0) return hipSuccess;
     const size_t bb = s.block_elems * elem_size(s.dtype);
     const dim3 grid((unsigned)groups), blk(64 * kWaves);
     const bool relu = s.act == LS_ACT_REGLU;
 #define LS_GUM(TT, AA)                                                                            \
     do {                                                                                          \
         if (s.prenorm)                                                                            \
-            hipLaunchKernelGGL((gateup_mfma_kernel<TT, AA, true>), grid, blk, 0, st, L.blocks, bb, \
+            hipLaunchKernelGGL((gateup_staged_kernel<TT, AA, true>), grid, blk, 0, st, L.blocks, bb, \
                                slot_table, L.bias, L.threshold, x, B, s.d, s.blk, s.n_blk, s.F,   \
                                idx, count, begin, end, a_buf);                                    \
         else                                                                                      \
-            hipLaunchKernelGGL((gateup_mfma_kernel<TT, AA, false>), grid, blk, 0, st, L.blocks,   \
+            hipLaunchKernelGGL((gateup_staged_kernel<TT, AA, false>), grid, blk, 0, st, L.blocks,   \
                                bb, slot_table, L.bias, L.threshold, x, B, s.d, s.blk, s.n_blk,    \
                                s.F, idx, count, begin, end, a_buf);                               \
     } while (0)

@@ -1,0 +1,78 @@
+"""Batched gate/up and down kernels at the sizes where their tiles and slices end: rows of one
+64-value step up to the longest slices, blocks that are no multiple of a K step, partial token
+groups, list entries that name no block, inputs beyond the 16-bit range."""
+import numpy as np
+import pytest
+
+import lsgen
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import paper_2609_03079_amd as lsffn  # noqa: E402
+from gpu_util import dev_f32, empty_f32, host, make_ffn, y_err  # noqa: E402
+
+# (d_model, block, n_blk): d = 64 is one step in one wave; 448 and 2880 leave ragged slices;
+# 2048 / 3072 / 4096 / 5120 / 6144 / 8192 are the last rows of the 4, 6, 8, 10, 12 and 16-step
+# slices; 8256 is past them
+SHAPES = [(64, 32, 4), (448, 32, 5), (2048, 64, 4), (2880, 64, 4), (3072, 32, 4), (4096, 32, 4), (5120, 64, 4),
+          (6144, 32, 4), (8192, 32, 4), (8256, 32, 4)]
+
+
+def _step(cfg, w, f, xs, ids):
+    B = len(xs)
+    idx = torch.tensor(ids, dtype=torch.int32, device="cuda")
+    cnt = torch.tensor([len(ids)], dtype=torch.int32, device="cuda")
+    out = empty_f32(B, cfg.d_model)
+    f.ls_sparse_ffn_step(0, dev_f32(xs), B, idx, cnt, 0, len(ids), out)
+    return host(out).astype(np.float64) - xs
+
+
+@pytest.mark.parametrize("dtype", [lsgen.DT_F16, lsgen.DT_BF16])
+@pytest.mark.parametrize("d,block,n_blk", SHAPES)
+def test_batched_step_at_the_edges(d, block, n_blk, dtype):
+    cfg = lsgen.CONFIGS["llama2_7b_ffn"].with_(n_layers=1, d_model=d, d_ff=block * n_blk, block=block, rank=64,
+                                               dtype=dtype)
+    f, (w,) = make_ffn(cfg, max_batch=8)
+    ids = [n_blk - 1, -1, 0, n_blk]            # two entries that name no block
+    blocks = np.array([n_blk - 1, 0], np.int32)
+    for B in (4, 5, 8):
+        xs = lsgen.tokens(cfg, 3, 1, B)[0]
+        y = _step(cfg, w, f, xs, ids)
+        for b in range(B):
+            ref = oracle.sparse_ffn(w, oracle.mlp_input(xs[b], cfg.prenorm), blocks, cfg.block, cfg.act, 0.0)
+            # y is read back as x_out - x: half an ulp of x_out (|x| <= 8: 2.4e-7 absolute) beside
+            # the products' error (2^-16 of an activation in bfloat16 parts)
+            scale = np.max(np.abs(ref))
+            assert y_err(y[b], ref) <= 5e-5 + 1e-6 / scale, (d, block, B, b)
+    f.close()
+
+
+def test_batched_inputs_beyond_float16():
+    """Without a prenorm an input may exceed the float16 range: the parts are taken of the input
+    scaled into it, so only the weights' type limits the result."""
+    cfg = lsgen.CONFIGS["llama2_7b_ffn"].with_(n_layers=1, d_model=1024, d_ff=256, block=32, rank=64, prenorm=False,
+                                               gate_bias=None)
+    f, (w,) = make_ffn(cfg, max_batch=4)
+    xs = lsgen.tokens(cfg, 5, 1, 4)[0]
+    xs *= np.array([[1.0], [1e6], [1e-4], [0.0]], np.float32)
+    ids = list(range(cfg.n_blk))
+    # gate/up alone (its activations; the down projection's operands keep the float16 range)
+    out, acts = empty_f32(4, cfg.d_model), empty_f32(4, cfg.d_ff)
+    idx = torch.tensor(ids, dtype=torch.int32, device="cuda")
+    cnt = torch.tensor([len(ids)], dtype=torch.int32, device="cuda")
+    f.ls_sparse_ffn_step(0, dev_f32(xs), 4, idx, cnt, 0, len(ids), out)
+    f.ls_debug_last_activations(acts)
+    a = host(acts).astype(np.float64)
+    g = xs.astype(np.float64) @ lsgen.decode_bits(w.gate, cfg.dtype).T
+    u = xs.astype(np.float64) @ lsgen.decode_bits(w.up, cfg.dtype).T
+    ref = np.maximum(g, 0) * u
+    for b in range(4):
+        # each factor within 2^-22 of the sum of its products' magnitudes (about 26 sigma at
+        # d = 1024), taken over the largest activation
+        assert np.max(np.abs(a[b] - ref[b])) <= 2e-5 * max(np.max(np.abs(ref[b])), 1e-30), b
+    f.close()
