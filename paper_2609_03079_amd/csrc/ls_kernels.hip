@@ -51,11 +51,10 @@ __global__ __launch_bounds__(64 * NW) void gemv_rows_kernel(const uint8_t* __res
 #pragma unroll
         for (int r = 0; r < R; ++r) acc[r][b] = 0.f;
     }
-    // PRE (up to 3 tokens): the input chunks are requested with the weights, so the products
-    // wait for one round trip; otherwise each chunk's input read is issued at its first use
-    // (measured at 8 tokens, requesting them early was slower: 2260 against 2272 tokens/s on
-    // the 13B shape), and so it is where they would take more than 32 registers of 16 bytes
-    constexpr bool PRE = B <= 3 && U * B * (V / 4) <= 32;
+    // PRE: the input chunks are requested with the weights, so the products wait for one round
+    // trip; where they would take more than 32 registers of 16 bytes each chunk's input read is
+    // issued at its first use
+    constexpr bool PRE = U * B * (V / 4) <= 32;
     constexpr int UX = PRE ? U : 1;
     for (int c0 = threadIdx.x; c0 < nchunk; c0 += 64 * NW * U) {
         u32x4 raw[U][R];
@@ -475,27 +474,37 @@ hipError_t launch_gateup_select(const Shape& s, const LayerDev& L, const float* 
 template <ls_dtype T, bool RMS>
 static hipError_t gemv_t(const void* W, int rows, int cols, int G, int rpw, const float* v, int B,
                          float* out, hipStream_t st) {
-    // four rows and eight waves per workgroup once the batch makes the input reads dominate;
-    // one row per workgroup below, on eight waves at batch 1 (against four: 7B shape 1664 ->
-    // 1681 tokens/s, 13B 1106 -> 1114 on the per-kernel path) and four at B = 2, 3
-    const int R = B >= 4 ? 4 : 1, NW = B >= 4 || B == 1 ? 8 : 4;
-    const dim3 grid((unsigned)((rows + R - 1) / R)), blk(64 * NW);
+    // one row per workgroup (four at B >= 4 had left most compute units without one), on four
+    // waves at B = 2, 3 and eight otherwise (B = 1 against four: 7B shape 1664 -> 1681 tokens/s,
+    // 13B 1106 -> 1114 on the per-kernel path)
+    const int NW = B == 2 || B == 3 ? 4 : 8;
+    const dim3 grid((unsigned)rows), blk(64 * NW);
     const uint8_t* w = static_cast<const uint8_t*>(W);
-    // a row longer than 4 loads per lane is read in one round of 8
-    const bool wide = cols / Wt<T>::V > 64 * NW * 4;
-#define LS_GEMV_U(NB, NR, NWV, U) hipLaunchKernelGGL((gemv_rows_kernel<T, NB, RMS, NR, NWV, U>), grid, blk, 0, st, w, rows, cols, G, rpw, v, out)
-#define LS_GEMV(NB, NR, NWV) LS_GEMV_U(NB, NR, NWV, 4)
+    const int per_lane = (cols / Wt<T>::V + 64 * NW - 1) / (64 * NW);
+#define LS_GEMV_U(NB, NWV, U) hipLaunchKernelGGL((gemv_rows_kernel<T, NB, RMS, 1, NWV, U>), grid, blk, 0, st, w, rows, cols, G, rpw, v, out)
+    // B <= 3: a row longer than 4 loads per lane is read in one round of 8; B >= 4: a round takes
+    // what the row has, up to the 32 input chunks that can be in flight
+#define LS_GEMV(NB, NWV) do { if (per_lane > 4) LS_GEMV_U(NB, NWV, 8); else LS_GEMV_U(NB, NWV, 4); } while (0)
+#define LS_GEMV_B(NB)                                                                  \
+    do {                                                                               \
+        constexpr int most = 32 / (NB * (Wt<T>::V / 4));                               \
+        if (per_lane <= 1 || most == 1) LS_GEMV_U(NB, 8, 1);                           \
+        else if (per_lane <= 2 || most == 2) LS_GEMV_U(NB, 8, 2);                      \
+        else if (per_lane <= 3 || most == 3) LS_GEMV_U(NB, 8, 3);                      \
+        else LS_GEMV_U(NB, 8, 4);                                                      \
+    } while (0)
     switch (B) {
-        case 1: if (wide) LS_GEMV_U(1, 1, 8, 8); else LS_GEMV(1, 1, 8); break;
-        case 2: if (wide) LS_GEMV_U(2, 1, 4, 8); else LS_GEMV(2, 1, 4); break;
-        case 3: if (wide) LS_GEMV_U(3, 1, 4, 8); else LS_GEMV(3, 1, 4); break;
-        case 4: LS_GEMV(4, 4, 8); break;
-        case 5: LS_GEMV(5, 4, 8); break;
-        case 6: LS_GEMV(6, 4, 8); break;
-        case 7: LS_GEMV(7, 4, 8); break;
-        case 8: LS_GEMV(8, 4, 8); break;
+        case 1: LS_GEMV(1, 8); break;
+        case 2: LS_GEMV(2, 4); break;
+        case 3: LS_GEMV(3, 4); break;
+        case 4: LS_GEMV_B(4); break;
+        case 5: LS_GEMV_B(5); break;
+        case 6: LS_GEMV_B(6); break;
+        case 7: LS_GEMV_B(7); break;
+        case 8: LS_GEMV_B(8); break;
         default: return hipErrorInvalidValue;
     }
+#undef LS_GEMV_B
 #undef LS_GEMV
 #undef LS_GEMV_U
     return hipGetLastError();
