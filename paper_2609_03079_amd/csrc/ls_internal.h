@@ -46,7 +46,7 @@ struct Shape {
     // when that matrix is no larger than the two factors in the weight type.
     int fold;
     // 1: batches of kMfmaMinBatch or more tokens use the matrix-core gate/up and down
-    // kernels when the shape allows (16-bit weights, block a multiple of 32).
+    // kernels when the shape and the list's length allow (16-bit weights).
     int batch_mfma = 1;
     // 1: row-level zero skip in the vector-ALU gate/up and down kernels (up rows only for
     // neurons with a nonzero gate output; down vectors only for groups with a nonzero
@@ -54,7 +54,7 @@ struct Shape {
     int zero_skip = 0;
 };
 
-constexpr int kMfmaMinBatch = 4;
+constexpr int kMfmaMinBatch = 2;
 
 // Fold decision: the product costs 4 n_blk d bytes, the factors (r d + n_blk r) elem bytes.
 inline int predictor_folds(int d, int r, int n_blk, ls_dtype t) {
@@ -137,18 +137,12 @@ struct StageArgs {
 hipError_t launch_stage_consumer(const Shape& s, const StageArgs& p, int grid, bool cooperative, hipStream_t st);
 
 // ---- matrix-core variants for B >= kMfmaMinBatch (ls_mfma.hip) ---------------------------
-bool mfma_path(const Shape& s, int B);
+bool gateup_on_mfma(const Shape& s, int B, int n);
+bool down_on_mfma(const Shape& s, int B, int n);
 hipError_t launch_gateup_mfma(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                               const float* x, int B, const int32_t* idx, const int32_t* count,
                               int begin, int end, float* a_buf, hipStream_t st);
 constexpr int kDownPartsMax = 8;  // list parts of the matrix-core down projection, at most
-// Layout of the matrix-core down projection: nt adjacent 16-column tiles per workgroup, the
-// list cut into `splits` parts (partial sums in the part buffer, added by a finish kernel),
-// `waves` waves per workgroup.
-struct DownLayout {
-    int nt, splits, waves;
-};
-DownLayout down_layout(const Shape& s, int B);
 hipError_t launch_down_mfma(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                             const float* a_buf, int B, const int32_t* idx, const int32_t* count,
                             int begin, int end, const float* x_in, float* x_acc, float* part,

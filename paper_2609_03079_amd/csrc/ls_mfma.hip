@@ -23,13 +23,6 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
-// fp32 -> bfloat16 bits, round to nearest even (NaN stays a quiet NaN)
-__device__ inline unsigned short bf16_rne(float x) {
-    const unsigned u = __float_as_uint(x);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (unsigned short)((u >> 16) | 0x40u);
-    return (unsigned short)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
-}
-
 // Split 8 fp32 values into hi and lo 16-bit operands of type T.
 template <ls_dtype T>
 struct Split;
@@ -58,13 +51,21 @@ struct Split<LS_F16> {
 template <>
 struct Split<LS_BF16> {
     typedef s16x8 vec;
+    // (the conversion instruction rounds to nearest even, two values at a time)
+    typedef __bf16 b16x2 __attribute__((ext_vector_type(2)));
     __device__ static inline void run(const float* x, vec& hi, vec& lo) {
+        u32x4 h4, l4;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const unsigned short h = bf16_rne(x[i]);
-            hi[i] = (short)h;
-            lo[i] = (short)bf16_rne(x[i] - __uint_as_float((unsigned)h << 16));
+        for (int i = 0; i < 4; ++i) {
+            const b16x2 h = {(__bf16)x[2 * i], (__bf16)x[2 * i + 1]};
+            const uint32_t hw = __builtin_bit_cast(uint32_t, h);
+            const b16x2 l = {(__bf16)(x[2 * i] - __uint_as_float(hw << 16)),
+                             (__bf16)(x[2 * i + 1] - __uint_as_float(hw & 0xffff0000u))};
+            h4[i] = hw;
+            l4[i] = __builtin_bit_cast(uint32_t, l);
         }
+        hi = from_raw(h4);
+        lo = from_raw(l4);
     }
     __device__ static inline vec from_raw(const u32x4& r) {
         vec v;
@@ -89,6 +90,19 @@ __device__ __forceinline__ f32x4 gload_x(const float* uniform_base, uint32_t byt
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
     return *(gf4_ptr)((const char*)(((uint64_t)hi << 32) | lo) + byte_off);
+}
+
+// sum of N (a power of two) values, pairwise
+template <int N>
+__device__ __forceinline__ float tree_sum(const float (&v)[N]) {
+    float t[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) t[i] = v[i];
+#pragma unroll
+    for (int n = N / 2; n > 0; n /= 2)
+#pragma unroll
+        for (int i = 0; i < n; ++i) t[i] += t[i + n];
+    return t[0];
 }
 
 // a barrier that orders LDS only: global loads already issued stay in flight
@@ -238,23 +252,22 @@ __global__ __launch_bounds__(64 * kGuWaves) void gateup_mfma_kernel(
     vec xf[NF][NK];
     float unscale = 1.f;
     {
-        float ss = 0.f, mx = 0.f;
+        float s4[4], mx = 0.f;  // four short chains: the scale's error goes into every sum
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s4[i] = 0.f;
 #pragma unroll
         for (int s = 0; s < NK; ++s)
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const float v = s < nst ? xv[s][i >> 2][i & 3] : 0.f;
                 xv[s][i >> 2][i & 3] = v;
-                ss = fmaf(v, v, ss);
                 if (T == LS_F16 && fabsf(v) < INFINITY) mx = fmaxf(mx, fabsf(v));
             }
         // lanes l, l + 8, l + 16, ... hold the same slot
+        if (T == LS_F16) {
 #pragma unroll
-        for (int off = 8; off < 64; off <<= 1) {
-            ss += __shfl_xor(ss, off, 64);
-            if (T == LS_F16) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+            for (int off = 8; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
         }
-        if (lane < 8) pss[wave][lane] = ss;
         int ex = 0;
         if (T == LS_F16 && mx > 0.f) {
             ex = (int)((__float_as_uint(mx) >> 23) & 0xffu) - 127;  // a subnormal maximum: -127
@@ -266,6 +279,8 @@ __global__ __launch_bounds__(64 * kGuWaves) void gateup_mfma_kernel(
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 float v0 = xv[s][j >> 1][(2 * j) & 3], v1 = xv[s][j >> 1][(2 * j + 1) & 3];
+                s4[(2 * j) & 3] = fmaf(v0, v0, s4[(2 * j) & 3]);
+                s4[(2 * j + 1) & 3] = fmaf(v1, v1, s4[(2 * j + 1) & 3]);
                 if (T == LS_F16) v0 = ldexpf(v0, -ex), v1 = ldexpf(v1, -ex);
                 // slot q of fragment f is part (8 f + q) / BP
                 float p0[P], p1[P];
@@ -296,6 +311,10 @@ __global__ __launch_bounds__(64 * kGuWaves) void gateup_mfma_kernel(
             if (s + 1 < NK) asm volatile("" : "+v"(xv[s + 1][0]), "+v"(xv[s + 1][1]));
             __builtin_amdgcn_sched_barrier(0);
         }
+        float ss = tree_sum<4>(s4);
+#pragma unroll
+        for (int off = 8; off < 64; off <<= 1) ss += __shfl_xor(ss, off, 64);
+        if (lane < 8) pss[wave][lane] = ss;
     }
     lds_barrier_m();
     // the finishing threads' token and its RMS scale
@@ -303,7 +322,10 @@ __global__ __launch_bounds__(64 * kGuWaves) void gateup_mfma_kernel(
     float sc = 1.f;
     if (rms) {
         float q = 0.f;
-        for (int w = 0; w < W; ++w) q += pss[w][ft & (BP - 1)];
+        float qw[kGuWaves];
+#pragma unroll
+        for (int w = 0; w < kGuWaves; ++w) qw[w] = w < W ? pss[w][ft & (BP - 1)] : 0.f;
+        q = tree_sum<kGuWaves>(qw);
         sc = rms_scale(q, d);
     }
 
@@ -356,17 +378,23 @@ __global__ __launch_bounds__(64 * kGuWaves) void gateup_mfma_kernel(
         // which the finishing wave joins after its reads
         lds_barrier_m();
         if (wave == it % W && ft < B) {
-            float g = 0.f, uv = 0.f;
-            for (int w = 0; w < W; ++w)
+            // the waves' sums pairwise, the smallest part first (a loop: its reads must not take the
+            // registers that hold the loads in flight)
+            float gu[2] = {0.f, 0.f};
+#pragma unroll 1
+            for (int pm = 2 * P - 1; pm >= 0; --pm) {
+                const int m = pm & 1, q = (pm >> 1) * BP + (ft & (BP - 1));
+                float sw[kGuWaves];
 #pragma unroll
-                for (int p = P - 1; p >= 0; --p) {
-                    const int q = p * BP + (ft & (BP - 1));
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        g += part[it & 1][w][0][q >> 3][h][q & 7][fr];
-                        uv += part[it & 1][w][1][q >> 3][h][q & 7][fr];
-                    }
+                for (int w = 0; w < kGuWaves; ++w) {
+                    const float s = part[it & 1][w][m][q >> 3][0][q & 7][fr] + part[it & 1][w][m][q >> 3][1][q & 7][fr];
+                    sw[w] = w < W ? s : 0.f;  // (a wave that is not there wrote nothing)
                 }
+                const float t = tree_sum<kGuWaves>(sw);
+                if (m) gu[1] += t;
+                else gu[0] += t;
+            }
+            float g = gu[0], uv = gu[1];
             const int e = begin + gi / gpe, r0 = (gi % gpe) * 8;
             float a = 0.f;
             if (slot >= 0) {
@@ -391,8 +419,6 @@ __global__ __launch_bounds__(64 * kGuWaves) void gateup_mfma_kernel(
 // ---- gate/up, any d ---------------------------------------------------------------------------------
 constexpr int kWaves = 4;     // gate/up: waves per workgroup
 constexpr int kRowsW = 32 / kWaves;  // gate/up: staged rows loaded by each wave per chunk
-constexpr int kUnrollDn = 4;  // down: (entry, K step) items in flight per wave, at most
-constexpr int kWavesDn = 16;  // down: waves per workgroup (one 16-column tile)
 
 // One workgroup per group of 16 neurons (rows r0..r0+15 of one list entry).  The gate and up
 // rows of the group stream through LDS in chunks of 512 K values: each load instruction reads
@@ -550,8 +576,203 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(kGu
     }
 }
 
-// One workgroup per NT adjacent 16-column tiles of y and part of the list; its waves split
-// that part's entries.  The down piece of a block for one 16-column tile is [blk/8][16][8]:
+constexpr int kWavesDn = 16;  // down: waves per workgroup
+constexpr int kDnTiles = 4;   // down: 16-column tiles per workgroup, at most (d is a multiple of 64)
+
+// ---- down projection ------------------------------------------------------------------------------------
+// One workgroup per NT adjacent 16-column tiles of y and part of the list; its waves share
+// that part's work items.  The down piece of a block for one tile is [blk/8][16][8]: a chunk
+// of 8 neurons is 256 contiguous bytes, 16 columns of 16 bytes, and the pieces of adjacent tiles
+// are adjacent.  An item is four consecutive chunks of the part's neurons in list order (a K step
+// of 32; lane group l / 16 holds chunk l / 16, so an item may cross from one entry into the next
+// and any block size works), for every tile of the workgroup: a wave loads the item's activations
+// once for NT weight fragments.  Those reads come from L2 but through the same per-CU path
+// as the weights, which bounds these kernels: at 8 tokens they are a quarter of the weights'
+// bytes at 4 tiles, and half at 2.  With the finish launch, 13B shape at B = 8 (138 blocks, 91
+// MB) 24.2 -> 20.5 us, Mistral-7B shape at B = 4 with a ReLU gate (105 blocks, 110 MB) 31.8 ->
+// 24 us against two tiles and eight parts.
+//
+// The 16 columns of operand B hold the activations' parts: BP (4 or 8) tokens each, part
+// (l % 16) / BP (+ 16 / BP in a second fragment, for three parts of 8 tokens).  float16 parts are
+// scaled per token by the largest magnitude the wave has met so far (a power of two; the sums
+// are rescaled when it grows), so that they neither overflow nor go subnormal, and the second
+// part by 2^11.  Two items are in flight per wave.
+//
+// With splits > 1 the list range is cut into `splits` equal parts (workgroup group + n_groups *
+// part); each part's sum goes to part_out[part][token][column] and down_finish_kernel adds the
+// parts in order.
+template <ls_dtype T, int BP, int NT>
+__global__ __launch_bounds__(64 * kWavesDn) void down_mfma_kernel(
+    const uint8_t* __restrict__ blocks, size_t block_bytes, const int32_t* __restrict__ slot_table,
+    const float* __restrict__ a_buf, int B, int F, int d, int blk, int n_blk,
+    const int32_t* __restrict__ idx, const int32_t* __restrict__ count, int begin, int end,
+    const float* __restrict__ x_in, float* __restrict__ x_acc, int splits,
+    float* __restrict__ part_out, uint32_t cpe_magic) {
+    using S = Split<T>;
+    typedef typename S::vec vec;
+    constexpr int P = Part<T>::kParts;
+    constexpr int PF = 16 / BP;              // parts of one fragment
+    constexpr int NF = (P + PF - 1) / PF;
+    const int n_groups = d / (kColTile * NT);
+    const int grp = (int)blockIdx.x % n_groups, sp = (int)blockIdx.x / n_groups;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    constexpr int n_waves = kWavesDn;
+    const int len = max(0, list_end_m(count, end, n_blk) - begin);
+    const int e0 = begin + (int)((long)len * sp / splits);
+    const int e1 = begin + (int)((long)len * (sp + 1) / splits);
+    const size_t piece = (size_t)blk * kColTile * 2;  // bytes of one tile's piece
+    const size_t down_off = (size_t)2 * blk * d * 2 + (size_t)grp * NT * piece + (size_t)(lane & 15) * 16;
+    // the cache slot of every entry of the part (-1: invalid id or absent), resolved once
+    __shared__ int slots[kMaxBlocks];
+    for (int e = e0 + (int)threadIdx.x; e < e1; e += (int)blockDim.x) {
+        const int b = idx[e];
+        slots[e - e0] = (b < 0 || b >= n_blk) ? -1 : (slot_table ? slot_table[b] : b);
+    }
+    __syncthreads();
+    const int col = lane & 15;
+    const int tok = col & (BP - 1), prt = col / BP;
+    const uint32_t cpe = (uint32_t)blk / 8u;  // chunks per entry
+    const uint32_t chunks = (uint32_t)(e1 - e0) * cpe;
+    const int items = (int)((chunks + 3u) / 4u);
+    const float* arow = a_buf + (size_t)(tok < B ? tok : 0) * F + (size_t)e0 * blk;
+
+    struct Item {
+        u32x4 w[NT];
+        f32x4 a[2];
+        bool live;
+    };
+    auto load_item = [&](Item& t, int it) {
+        const uint32_t f = 4u * (uint32_t)it + (uint32_t)(lane >> 4);
+        t.live = f < chunks;
+        const uint32_t fc = t.live ? f : 0u;
+        // f / cpe by multiplication (cpe_magic = ceil(2^32 / cpe), exact while chunks cpe < 2^32)
+        const uint32_t e = cpe_magic ? __umulhi(fc, cpe_magic) : fc / cpe;
+        const int slot = slots[e];
+        t.live = t.live && slot >= 0;  // an invalid or absent block contributes nothing
+        const uint8_t* src = blocks + (size_t)(slot < 0 ? 0 : slot) * block_bytes + down_off + (size_t)(fc - e * cpe) * 256;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) t.w[j] = ld_stream(reinterpret_cast<const u32x4*>(src + j * piece));
+        const f32x4* ap = reinterpret_cast<const f32x4*>(arow + (size_t)fc * 8);
+        t.a[0] = ap[0];
+        t.a[1] = ap[1];
+    };
+    f32x4v c[NT][NF];
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) c[j][f] = f32x4v{0.f, 0.f, 0.f, 0.f};
+    // float16: exponent of the scale (of the largest magnitude so far, not below 2^-100), the same
+    // in a token's lanes, and the magnitude that it holds up to
+    int ex = -100;
+    float s1 = ldexpf(1.f, -ex), limit = ldexpf(1.f, ex + 1);
+    auto run_item = [&](Item& t) {
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = t.live ? t.a[i >> 2][i & 3] : 0.f;
+        float mx = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) mx = fmaxf(fmaxf(mx, fabsf(v[i])), fabsf(v[i + 1]));
+        if (__any(T == LS_F16 ? mx >= limit : mx == INFINITY)) {  // rare
+            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            if (T == LS_F16) {
+                const int eg = max(ex, min(127, (int)((__float_as_uint(mx) >> 23) & 0xffu) - 127));
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) c[j][0][i] = ldexpf(c[j][0][i], ex - eg);
+                ex = eg;
+                s1 = ldexpf(1.f, -ex);
+                limit = ldexpf(1.f, ex + 1);
+            }
+            if (prt > 0) {  // an infinity is its first part alone
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = fabsf(v[i]) < INFINITY ? v[i] : 0.f;
+            }
+        }
+        vec pt[NF];
+        if constexpr (T == LS_F16) {
+            typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+            u32x4 words;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float a0 = v[2 * q], a1 = v[2 * q + 1];
+                const f16x2 h = {(_Float16)(a0 * s1), (_Float16)(a1 * s1)};
+                const float s2 = s1 * 2048.f;
+                const f16x2 m = {(_Float16)fmaf((float)h.x, -2048.f, a0 * s2), (_Float16)fmaf((float)h.y, -2048.f, a1 * s2)};
+                words[q] = prt ? __builtin_bit_cast(uint32_t, m) : __builtin_bit_cast(uint32_t, h);
+            }
+            pt[0] = S::from_raw(words);
+        } else {
+            auto rest = [](float x) { return x - __uint_as_float(__float_as_uint(x) & 0xffff0000u); };
+            u32x4 words[NF];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float a0 = v[2 * q], a1 = v[2 * q + 1];
+                const float b0 = rest(a0), b1 = rest(a1), d0 = rest(b0), d1 = rest(b1);
+                auto pack = [](float lo, float hi) { return (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xffff0000u); };
+                const uint32_t w0 = pack(a0, a1), w1 = pack(b0, b1), w2 = pack(d0, d1);
+                words[0][q] = prt == 0 ? w0 : (prt == 1 ? w1 : w2);
+                if (NF > 1) words[NF - 1][q] = w2;  // (its second half is never used)
+            }
+#pragma unroll
+            for (int f = 0; f < NF; ++f) pt[f] = S::from_raw(words[f]);
+        }
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            u32x4 raw = t.w[j];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) raw[i] = t.live ? raw[i] : 0u;
+            const vec wv = S::from_raw(raw);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) c[j][f] = S::mfma(wv, pt[f], c[j][f]);
+        }
+    };
+    Item ta, tb;
+    int it = wave;
+    if (it < items) load_item(ta, it);
+    for (; it < items; it += 2 * n_waves) {
+        if (it + n_waves < items) load_item(tb, it + n_waves);
+        run_item(ta);
+        if (it + n_waves >= items) break;
+        if (it + 2 * n_waves < items) load_item(ta, it + 2 * n_waves);
+        run_item(tb);
+    }
+    // lane l: columns 4 (l / 16) + i of tile j, slot l % 16
+    __shared__ __attribute__((aligned(16))) float part[kWavesDn][NT][NF][16][16];
+    const float k = T == LS_F16 ? ldexpf(1.f, ex - Part<T>::kShift * prt) : 1.f;
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            f32x4v v = c[j][f];
+            if (T == LS_F16) v *= k;
+            *reinterpret_cast<f32x4v*>(&part[wave][j][f][col][4 * (lane >> 4)]) = v;
+        }
+    __syncthreads();
+    for (int q = (int)threadIdx.x; q < NT * 16 * B; q += (int)blockDim.x) {
+        const int t = q / (16 * NT), j = (q / 16) % NT, m16 = q % 16;
+        float yp[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            float yw[kWavesDn];
+#pragma unroll
+            for (int w = 0; w < kWavesDn; ++w) yw[w] = part[w][j][p / PF][(p % PF) * BP + t][m16];
+            yp[p] = tree_sum<kWavesDn>(yw);
+        }
+        float y = yp[P - 1];
+#pragma unroll
+        for (int p = P - 2; p >= 0; --p) y += yp[p];
+        const size_t m = (size_t)t * d + (size_t)(grp * NT + j) * kColTile + m16;
+        if (splits == 1)
+            x_acc[m] = (begin == 0 ? x_in[m] : x_acc[m]) + y;
+        else
+            part_out[(size_t)sp * B * d + m] = y;
+    }
+}
+
+// The batched down projection of thresholded gates (keeps_order below): one workgroup per NT
+// adjacent 16-column tiles of y and part of the list; its waves split that part's entries.  The down piece of a block for one 16-column tile is [blk/8][16][8]:
 // K step s of an entry is the contiguous kilobyte of chunks 64 s .. 64 s + 63, exactly one A
 // fragment, and the pieces of adjacent tiles are adjacent.  A wave loads the activations of
 // a work item once for its NT fragments: every workgroup reads the whole part's activations
@@ -563,14 +784,13 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(kGu
 // down_finish_kernel adds the parts in order.  The wave count is blockDim.x / 64 (at most
 // kWavesDn, and at most kWavesDn / NT with NT > 1).
 template <ls_dtype T, int NT, int KU>
-__global__ __launch_bounds__(64 * kWavesDn) void down_mfma_kernel(
+__global__ __launch_bounds__(64 * kWavesDn) void down_ordered_kernel(
     const uint8_t* __restrict__ blocks, size_t block_bytes, const int32_t* __restrict__ slot_table,
     const float* __restrict__ a_buf, int B, int F, int d, int blk, int n_blk,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ count, int begin, int end,
     const float* __restrict__ x_in, float* __restrict__ x_acc, int splits,
     float* __restrict__ part_out) {
     using S = Split<T>;
-    static_assert(KU >= 1 && KU <= kUnrollDn, "items in flight per wave");
     constexpr int kU = KU;
     const int n_tiles = d / (kColTile * NT);
     const int tile = (int)blockIdx.x % n_tiles, sp = (int)blockIdx.x / n_tiles;
@@ -656,21 +876,55 @@ __global__ __launch_bounds__(64 * kWavesDn) void down_mfma_kernel(
     }
 }
 
-// x_acc[m] = (x_in or x_acc)[m] + the parts' sums for m in order of part
-__global__ __launch_bounds__(256) void down_finish_kernel(const float* __restrict__ part, int splits,
-                                                          int n, const float* __restrict__ x_in,
+// x_acc[m] = (x_in or x_acc)[m] + the parts' sums for m in order of part; every load is issued
+// before the first sum (one round trip instead of one per part)
+template <int SP>
+__global__ __launch_bounds__(256) void down_finish_kernel(const float* __restrict__ part, int n,
+                                                          const float* __restrict__ x_in,
                                                           float* __restrict__ x_acc, int first) {
     const int m = (int)blockIdx.x * 256 + (int)threadIdx.x;
     if (m >= n) return;
+    const float x = first ? x_in[m] : x_acc[m];
+    float v[SP];
+#pragma unroll
+    for (int p = 0; p < SP; ++p) v[p] = part[(size_t)p * n + m];
     float y = 0.f;
-    for (int p = 0; p < splits; ++p) y += part[(size_t)p * n + m];
-    x_acc[m] = (first ? x_in[m] : x_acc[m]) + y;
+#pragma unroll
+    for (int p = 0; p < SP; ++p) y += v[p];
+    x_acc[m] = x + y;
 }
 
 }  // namespace
 
-bool mfma_path(const Shape& s, int B) {
-    return B >= kMfmaMinBatch && B <= 16 && s.dtype != LS_F32 && s.blk % 32 == 0 && s.d % 32 == 0;
+// The resident kernel's registers hold up to 16 steps of 64 values a wave beside the loads in
+// flight, but only 12 where the parts take three fragments (bfloat16, 5 to 8 tokens).
+static bool resident_ok(const Shape& s, int B) {
+    const int nk = s.dtype == LS_BF16 && B > 4 ? 12 : 16;
+    return s.d <= 64 * nk * kGuWaves;
+}
+
+// A thresholded gate turns the last bit of a sum into a neuron kept or dropped, and in a stack a
+// neuron into another block of the next layer's list.  Where such a gate was batched on the
+// matrix cores with two-part activations (4 tokens or more, whole K steps a block), the sums
+// keep the order and the parts they have always had, so its decisions stay the same.
+static bool keeps_order(const Shape& s, int B) {
+    return s.act == LS_ACT_SWIGLU_THRESH && B >= 4 && s.blk % 32 == 0;
+}
+
+// Whether gate/up and down run here for B tokens and a list of up to n entries.  From 4 tokens on
+// always, where a kernel takes the shape; at 2 and 3 once the list's weights are long enough to
+// pay for the kernels' start (about 4 us more than the vector-ALU kernels').  Measured with 2
+// tokens, gate/up: 45 MB 14.6 us on the vector ALU against 15.7 here, 71 MB 21.7 / 20.0, 235 MB
+// 46.3 / 43.2; 3 tokens: 22 MB 11.9 / 12.2, 45 MB 18.1 / 16.6; down, 2 tokens: 45 MB 13.8 / 15.5,
+// 88 MB 25.0 / 20.8; 3 tokens: 22 MB 10.6 / 12.1, 45 MB 18.4 / 15.5.
+static bool mfma_shape(const Shape& s, int B) {
+    return B >= kMfmaMinBatch && s.dtype != LS_F32 && (resident_ok(s, B) || (B >= 4 && s.blk % 32 == 0));
+}
+bool gateup_on_mfma(const Shape& s, int B, int n) {
+    return mfma_shape(s, B) && (B >= 4 || 4.0 * n * s.blk * s.d >= (B == 2 ? 64e6 : 30e6));
+}
+bool down_on_mfma(const Shape& s, int B, int n) {
+    return mfma_shape(s, B) && (B >= 4 || 2.0 * n * s.blk * s.d >= (B == 2 ? 60e6 : 32e6));
 }
 
 template <ls_dtype T, int BP>
@@ -697,7 +951,7 @@ static hipError_t gateup_resident_bp(const Shape& s, const LayerDev& L, const in
     else if (steps <= 8 * kGuWaves) LS_GUR(8);
     else if (steps <= 10 * kGuWaves) LS_GUR(10);
     else if (steps <= 12 * kGuWaves) LS_GUR(12);
-    else if (steps <= 16 * kGuWaves) LS_GUR(16);
+    else if constexpr (T == LS_F16 || BP <= 4) LS_GUR(16);
     else return hipErrorInvalidValue;
 #undef LS_GUR
 #undef LS_GUR_K
@@ -708,22 +962,16 @@ template <ls_dtype T>
 static hipError_t gateup_resident_t(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* x, int B,
                                     const int32_t* idx, const int32_t* count, int begin, int end, float* a_buf,
                                     hipStream_t st) {
+    if (B <= 2) return gateup_resident_bp<T, 2>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, st);
     if (B <= 4) return gateup_resident_bp<T, 4>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, st);
     return gateup_resident_bp<T, 8>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, st);
-}
-
-// The resident kernel's registers hold up to 16 steps of 64 values a wave beside the loads in
-// flight, but only 12 where the parts take three fragments (bfloat16, 5 to 8 tokens).
-static bool resident_ok(const Shape& s, int B) {
-    const int nk = s.dtype == LS_BF16 && B > 4 ? 12 : 16;
-    return s.d <= 64 * nk * kGuWaves;
 }
 
 hipError_t launch_gateup_mfma(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                               const float* x, int B, const int32_t* idx, const int32_t* count,
                               int begin, int end, float* a_buf, hipStream_t st) {
     if (end <= begin) return hipSuccess;
-    if (resident_ok(s, B)) {
+    if (!keeps_order(s, B) && resident_ok(s, B)) {
         return s.dtype == LS_F16 ? gateup_resident_t<LS_F16>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, st)
                                  : gateup_resident_t<LS_BF16>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, st);
     }
@@ -755,57 +1003,99 @@ hipError_t launch_gateup_mfma(const Shape& s, const LayerDev& L, const int32_t* 
     return hipGetLastError();
 }
 
-DownLayout down_layout(const Shape& s, int B) {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-        cus = 256;
-    // Chosen from launch times over list lengths on the three model shapes (B = 4 and 8):
-    // 32 columns per workgroup wherever the activation reads are a large share of a
-    // workgroup's bytes; tiles that do not fill whole rounds of the CUs (d = 5120) and 128-row
-    // blocks (one block's piece of a tile is 4 KB) take 8 list parts of 4 waves; 64-row blocks
-    // at d = 4096 take 2 parts of 8 waves at B = 8 and one 16-column tile per workgroup, no
-    // parts, below.
-    if ((s.d / kColTile) % cus != 0 || s.blk >= 128) return DownLayout{2, 8, 4};
-    if (B >= 8 && (s.d / (2 * kColTile)) * 2 % cus == 0) return DownLayout{2, 2, 8};
-    return DownLayout{1, 1, kWavesDn};
+// List parts of the down projection: as many as the compute units hold at once, one workgroup of
+// 64 columns and one part each.
+static int down_splits(const Shape& s) {
+    return std::min(kDownPartsMax, std::max(1, cu_count() / (s.d / (kColTile * kDnTiles))));
+}
+
+template <ls_dtype T, int BP, int NT>
+static void down_mfma_nt(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* a_buf, int B,
+                         const int32_t* idx, const int32_t* count, int begin, int end, const float* x_in, float* x_acc,
+                         int splits, float* part, hipStream_t st) {
+    const size_t bb = s.block_elems * elem_size(s.dtype);
+    const uint32_t cpe = (uint32_t)s.blk / 8u;
+    const bool exact = cpe > 1 && (uint64_t)(s.F / 8) * cpe < (1ull << 32);
+    const uint32_t magic = exact ? 0xffffffffu / cpe + 1u : 0u;
+    hipLaunchKernelGGL((down_mfma_kernel<T, BP, NT>), dim3((unsigned)(s.d / (kColTile * NT) * splits)),
+                       dim3(64 * kWavesDn), 0, st, L.blocks, bb, slot_table, a_buf, B, s.F, s.d, s.blk, s.n_blk, idx,
+                       count, begin, end, x_in, x_acc, splits, part, magic);
+}
+
+// One tile per workgroup and the whole list needs no finish launch (about 2.5 us) but reads and
+// splits the activations once per 16 columns instead of once per 64, and its 16 waves leave room
+// for one workgroup per compute unit.  Measured at the longest list the call allows: d = 4096,
+// B = 4: 5 MB of weights 7.4 us against 9.0 with four tiles, 22 MB 12.1 / 12.0, 45 MB 15.1 / 15.4;
+// d = 1984, B = 8: 6 MB 9.4 / 10, 17 MB 15.4 / 11.5; d = 5120 (320 tiles, 256 units), B = 2:
+// 71 MB 32 / 18.
+static bool down_one_tile(const Shape& s, int B, int n) {
+    return s.d / kColTile <= cu_count() && 2.0 * B * n * s.blk * s.d <= 80e6;
+}
+
+template <ls_dtype T, int BP>
+static void down_mfma_bp(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* a_buf, int B,
+                         const int32_t* idx, const int32_t* count, int begin, int end, const float* x_in, float* x_acc,
+                         int splits, float* part, bool one, hipStream_t st) {
+    if (one)
+        down_mfma_nt<T, BP, 1>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, 1, part, st);
+    else
+        down_mfma_nt<T, BP, kDnTiles>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, st);
+}
+
+// The order of a thresholded gate's down projection: list parts and waves by shape (tiles that
+// do not fill whole rounds of the CUs and 128-row blocks take 8 parts of 4 waves, 64-row blocks
+// at B = 8 2 parts of 8, the rest one part of 16); the tiles per workgroup are free.  Returns the
+// number of parts.
+template <ls_dtype T>
+static int down_ordered_t(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* a_buf, int B,
+                          const int32_t* idx, const int32_t* count, int begin, int end, const float* x_in,
+                          float* x_acc, float* part, hipStream_t st) {
+    const size_t bb = s.block_elems * elem_size(s.dtype);
+    const int cus = cu_count() > 0 ? cu_count() : 256;
+    int splits = 1, waves = kWavesDn;
+    if (part) {
+        if ((s.d / kColTile) % cus != 0 || s.blk >= 128) splits = 8, waves = 4;
+        else if (B >= 8 && (s.d / (2 * kColTile)) * 2 % cus == 0) splits = 2, waves = 8;
+    }
+#define LS_DNO(NT, KU)                                                                                                 \
+    hipLaunchKernelGGL((down_ordered_kernel<T, NT, KU>), dim3((unsigned)(s.d / (kColTile * NT) * splits)),             \
+                       dim3(64 * waves), 0, st, L.blocks, bb, slot_table, a_buf, B, s.F, s.d, s.blk, s.n_blk, idx,     \
+                       count, begin, end, x_in, x_acc, splits, part)
+    if (splits == 8) LS_DNO(4, 2);
+    else if (splits == 2) LS_DNO(2, 4);
+    else LS_DNO(1, 2);
+#undef LS_DNO
+    return splits;
 }
 
 hipError_t launch_down_mfma(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                             const float* a_buf, int B, const int32_t* idx, const int32_t* count,
                             int begin, int end, const float* x_in, float* x_acc, float* part,
                             hipStream_t st) {
-    const size_t bb = s.block_elems * elem_size(s.dtype);
-    DownLayout lay = down_layout(s, B);
-    if (!part) lay = DownLayout{1, 1, kWavesDn};
-    const dim3 grid((unsigned)(s.d / (kColTile * lay.nt) * lay.splits)), blk(64 * lay.waves);
-    // items in flight per wave: 4 with eight waves per workgroup, else 2 (measured at B = 4 and
-    // 8 on the three shapes: 2 against 4 gave the 13B shape at B = 8 2357 -> 2367 tokens/s, the
-    // Mistral-7B shape at B = 4 1208 -> 1230, the 7B shape at B = 4 2719 -> 2757, and lost 1.5%
-    // on the 7B shape at B = 8, the eight-wave layout; 6 lost everywhere)
-    const int ku = lay.waves == 8 ? 4 : 2;
-#define LS_DNM(TT, NT, KU)                                                                                   \
-    hipLaunchKernelGGL((down_mfma_kernel<TT, NT, KU>), grid, blk, 0, st, L.blocks, bb, slot_table, a_buf, B, \
-                       s.F, s.d, s.blk, s.n_blk, idx, count, begin, end, x_in, x_acc, lay.splits, part)
-#define LS_DNT(TT)                                     \
-    do {                                               \
-        if (lay.nt == 1) LS_DNM(TT, 1, 2);             \
-        else if (ku == 4) LS_DNM(TT, 2, 4);            \
-        else LS_DNM(TT, 2, 2);                         \
-    } while (0)
-    if (s.dtype == LS_F16)
-        LS_DNT(LS_F16);
+    const bool one = down_one_tile(s, B, end - begin);
+    int splits = part && !one ? down_splits(s) : 1;
+    if (keeps_order(s, B))
+        splits = s.dtype == LS_F16 ? down_ordered_t<LS_F16>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, part, st)
+                                   : down_ordered_t<LS_BF16>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, part, st);
+    else if (s.dtype == LS_F16)
+        down_mfma_bp<LS_F16, 8>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, one, st);
+    else if (s.dtype == LS_BF16 && B <= 4)
+        down_mfma_bp<LS_BF16, 4>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, one, st);
     else if (s.dtype == LS_BF16)
-        LS_DNT(LS_BF16);
+        down_mfma_bp<LS_BF16, 8>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, one, st);
     else
         return hipErrorInvalidValue;
-#undef LS_DNT
-#undef LS_DNM
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || lay.splits == 1) return e;
-    const int n = B * s.d;
-    hipLaunchKernelGGL(down_finish_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, lay.splits, n,
-                       x_in, x_acc, begin == 0 ? 1 : 0);
+    if (e != hipSuccess || splits == 1) return e;
+    const int n = B * s.d, first = begin == 0 ? 1 : 0;
+    const dim3 grid((unsigned)((n + 255) / 256)), blk(256);
+    switch (splits) {
+#define LS_FIN(SP) case SP: hipLaunchKernelGGL(down_finish_kernel<SP>, grid, blk, 0, st, part, n, x_in, x_acc, first); break
+        LS_FIN(2); LS_FIN(3); LS_FIN(4); LS_FIN(5); LS_FIN(6); LS_FIN(7); LS_FIN(8);
+#undef LS_FIN
+        default: return hipErrorInvalidValue;
+    }
+    static_assert(kDownPartsMax == 8, "a finish kernel per number of parts");
     return hipGetLastError();
 }
 

@@ -18,9 +18,9 @@ from gpu_util import dev_f32, empty_f32, host, make_ffn, y_err  # noqa: E402
 
 # (d_model, block, n_blk): d = 64 is one step in one wave; 448 and 2880 leave ragged slices;
 # 2048 / 3072 / 4096 / 5120 / 6144 / 8192 are the last rows of the 4, 6, 8, 10, 12 and 16-step
-# slices; 8256 is past them
+# slices; 8256 is past them; blocks of 8, 24 and 40 neurons share a K step with the next entry
 SHAPES = [(64, 32, 4), (448, 32, 5), (2048, 64, 4), (2880, 64, 4), (3072, 32, 4), (4096, 32, 4), (5120, 64, 4),
-          (6144, 32, 4), (8192, 32, 4), (8256, 32, 4)]
+          (6144, 32, 4), (8192, 32, 4), (8256, 32, 4), (64, 8, 5), (320, 40, 7), (1024, 24, 9), (2048, 128, 4)]
 
 
 def _step(cfg, w, f, xs, ids):
@@ -47,9 +47,52 @@ def test_batched_step_at_the_edges(d, block, n_blk, dtype):
             ref = oracle.sparse_ffn(w, oracle.mlp_input(xs[b], cfg.prenorm), blocks, cfg.block, cfg.act, 0.0)
             # y is read back as x_out - x: half an ulp of x_out (|x| <= 8: 2.4e-7 absolute) beside
             # the products' error (2^-16 of an activation in bfloat16 parts)
-            scale = np.max(np.abs(ref))
+            scale = max(np.max(np.abs(ref)), 1e-2)
             assert y_err(y[b], ref) <= 5e-5 + 1e-6 / scale, (d, block, B, b)
     f.close()
+
+
+@pytest.mark.parametrize("dtype", [lsgen.DT_F16, lsgen.DT_BF16])
+@pytest.mark.parametrize("B,d,block,n_blk", [
+    (2, 4096, 64, 130),   # long lists: 2 and 3 tokens on the matrix cores (gate/up and down)
+    (3, 4096, 64, 66),
+    (3, 4096, 64, 64),    # just below the down projection's length: gate/up there, down not
+    (5, 1024, 24, 240),   # parts that begin inside a K step
+    (6, 2880, 40, 90),
+    (8, 4096, 128, 24),
+])
+def test_long_lists_against_the_vector_path(B, d, block, n_blk, dtype):
+    """Lists long enough for the matrix cores, cut in parts, against the vector-ALU kernels."""
+    cfg = lsgen.CONFIGS["llama2_7b_ffn"].with_(n_layers=1, d_model=d, d_ff=block * n_blk, block=block, rank=64,
+                                               dtype=dtype)
+    f, (w,) = make_ffn(cfg, max_batch=B)
+    xs = lsgen.tokens(cfg, 3, 1, B)[0]
+    ids = list(range(n_blk))[::-1]
+    ids[1] = -1
+    y = _step(cfg, w, f, xs, ids)
+    f.ls_configure(lsffn.LS_CFG_BATCH_MFMA, 0)
+    ref = _step(cfg, w, f, xs, ids)
+    for b in range(B):
+        # both accumulate in fp32 (about 1e-6 of y); x_out - x adds an ulp of x_out each
+        assert y_err(y[b], ref[b]) <= 5e-6 + 1e-6 / np.max(np.abs(ref[b])), b
+    f.close()
+
+
+def test_batched_thresholded_gate_keeps_its_sums():
+    """A thresholded gate's batch (4 tokens or more, whole K steps) runs in the order of the two-part
+    kernels at every layout: against the vector path, few neurons may differ at the threshold."""
+    for d, block, n_blk, B in ((1024, 64, 12, 4), (4096, 64, 8, 8), (4096, 32, 12, 5), (512, 128, 6, 8)):
+        cfg = lsgen.CONFIGS["mistral_7b_ffn"].with_(n_layers=1, d_model=d, d_ff=block * n_blk, block=block, rank=64)
+        f, (w,) = make_ffn(cfg, max_batch=B)
+        xs = lsgen.tokens(cfg, 3, 1, B)[0]
+        ids = list(range(n_blk))
+        y = _step(cfg, w, f, xs, ids)
+        for b in range(B):
+            h = oracle.mlp_input(xs[b], cfg.prenorm)
+            ref = oracle.sparse_ffn(w, h, np.array(ids, np.int32), cfg.block, cfg.act, w.threshold)
+            # a neuron at the threshold: |a| <= 0.2544 * |u| against a sum of some hundred
+            assert y_err(y[b], ref) <= 5e-2, (d, block, B, b)
+        f.close()
 
 
 def test_batched_inputs_beyond_float16():
