@@ -10,10 +10,13 @@
 //
 // One workgroup per token.  The binary layers' tables and hyperplanes (33 KB) are copied into
 // LDS while the first layer runs, so the four dependent lookups after it do not go to memory.
-// The dot products are the only floating-point work: each of the 256 threads sums j = t,
-// t + 256, ... with fused multiply-adds in order, then a pairwise halving sum in LDS gives each
-// hash bit (a fixed order, so the codes are reproducible).  The four binary layers run in one
-// wave (lane b evaluates hash bit b; a ballot forms the bucket).
+// The dot products are the only floating-point work: 256 partial sums of j = t, t + 256, ... with
+// fused multiply-adds in order, then a pairwise halving sum gives each hash bit (a fixed order,
+// so the codes are reproducible).  The kernel is bound by latency (161 KB through one compute
+// unit), so the 8 hash bits are spread over four groups of 256 threads, two bits each, whose loads
+// of eight steps are in flight together, and only the first two halvings cross waves: 8 tokens at
+// d = 4096 with the selection after it 9.84 -> 9.34 us (launches take most of what is left).  The four binary layers run in one wave (lane b evaluates hash bit b; a
+// ballot forms the bucket).
 #include "ls_internal.h"
 
 namespace ls {
@@ -23,7 +26,8 @@ constexpr int kTau = 8;                // hash bits per layer
 constexpr int kDh = 256;               // binary feature width
 constexpr int kDhWords = kDh / 32;
 constexpr int kHashLayers = 5;
-constexpr int kThreads = 256;
+constexpr int kPart = 256;             // partial sums per hash bit
+constexpr int kThreads = 1024;         // kPart per pair of hash bits
 
 // bucket of a code whose bit b (hash bit b, 1 = +1) sits in bit b of `mask`: bit b has weight
 // 2^(7 - b)
@@ -37,50 +41,59 @@ __global__ __launch_bounds__(kThreads) void hash_predict_kernel(int d, int nblk,
                                                                const uint32_t* __restrict__ tables,
                                                                const uint8_t* __restrict__ head,
                                                                float* __restrict__ scores) {
-    __shared__ float part[kTau][kThreads];
+    __shared__ float part[kTau][kPart];
+    __shared__ float dots[kTau];
     __shared__ uint32_t tab[(kHashLayers - 1) * kDh * kDhWords];
     __shared__ uint32_t wb[(kHashLayers - 1) * kTau * kDhWords];
     __shared__ int last_bucket;
     const int t = threadIdx.x;
-    {
-        // 16-byte copies: tables 2048, hyperplanes 64
-        const uint4* src = reinterpret_cast<const uint4*>(tables);
-        uint4* dst = reinterpret_cast<uint4*>(tab);
-        constexpr int n_tab = (kHashLayers - 1) * kDh * kDhWords / 4;
-#pragma unroll
-        for (int i = 0; i < n_tab / kThreads; ++i) dst[t + kThreads * i] = src[t + kThreads * i];
-        constexpr int n_wb = (kHashLayers - 1) * kTau * kDhWords / 4;
-        if (t < n_wb) reinterpret_cast<uint4*>(wb)[t] = reinterpret_cast<const uint4*>(w_bin)[t];
-    }
+    static_assert(kThreads == kPart * kTau / 2, "two hash bits per group of threads");
+    const int p = t & (kPart - 1), b0 = t / kPart * 2;  // this thread's partial sum and first hash bit
     const float* xt = x + (size_t)blockIdx.x * d;
-    float acc[kTau];
+    float acc0 = 0.f, acc1 = 0.f;
+    constexpr int kSteps = 8;  // loads in flight together (16 were no faster)
+    for (int j0 = p; j0 < d; j0 += kPart * kSteps) {
+        float xv[kSteps];
+        float2 wv[kSteps];
 #pragma unroll
-    for (int b = 0; b < kTau; ++b) acc[b] = 0.f;
-    for (int j = t; j < d; j += kThreads) {
-        const float xv = xt[j];
-        const float4 lo = *reinterpret_cast<const float4*>(w1 + (size_t)j * kTau);
-        const float4 hi = *reinterpret_cast<const float4*>(w1 + (size_t)j * kTau + 4);
-        acc[0] = fmaf(xv, lo.x, acc[0]);
-        acc[1] = fmaf(xv, lo.y, acc[1]);
-        acc[2] = fmaf(xv, lo.z, acc[2]);
-        acc[3] = fmaf(xv, lo.w, acc[3]);
-        acc[4] = fmaf(xv, hi.x, acc[4]);
-        acc[5] = fmaf(xv, hi.y, acc[5]);
-        acc[6] = fmaf(xv, hi.z, acc[6]);
-        acc[7] = fmaf(xv, hi.w, acc[7]);
-    }
-#pragma unroll
-    for (int b = 0; b < kTau; ++b) part[b][t] = acc[b];
-    __syncthreads();
-    for (int s = kThreads / 2; s >= 1; s >>= 1) {
-        if (t < s) {
-#pragma unroll
-            for (int b = 0; b < kTau; ++b) part[b][t] = part[b][t] + part[b][t + s];
+        for (int i = 0; i < kSteps; ++i) {
+            const int j = min(j0 + kPart * i, d - 1);
+            xv[i] = xt[j];
+            wv[i] = *reinterpret_cast<const float2*>(w1 + (size_t)j * kTau + b0);
         }
-        __syncthreads();
+        if (j0 == p) {
+            // 16-byte copies: tables 2048, hyperplanes 64
+            const uint4* src = reinterpret_cast<const uint4*>(tables);
+            uint4* dst = reinterpret_cast<uint4*>(tab);
+            constexpr int n_tab = (kHashLayers - 1) * kDh * kDhWords / 4;
+            static_assert(n_tab % kThreads == 0, "whole copies");
+#pragma unroll
+            for (int i = 0; i < n_tab / kThreads; ++i) dst[t + kThreads * i] = src[t + kThreads * i];
+            constexpr int n_wb = (kHashLayers - 1) * kTau * kDhWords / 4;
+            if (t < n_wb) reinterpret_cast<uint4*>(wb)[t] = reinterpret_cast<const uint4*>(w_bin)[t];
+        }
+#pragma unroll
+        for (int i = 0; i < kSteps; ++i) {
+            if (j0 + kPart * i < d) {
+                acc0 = fmaf(xv[i], wv[i].x, acc0);
+                acc1 = fmaf(xv[i], wv[i].y, acc1);
+            }
+        }
     }
+    part[b0][p] = acc0;
+    part[b0 + 1][p] = acc1;
+    __syncthreads();
+    // hash bit b by wave b: the halvings 128 and 64 from LDS, the rest between lanes
+    if (t < 64 * kTau) {
+        const int b = t >> 6, l = t & 63;
+        float v = (part[b][l] + part[b][l + 128]) + (part[b][l + 64] + part[b][l + 192]);
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1) v = v + __shfl_down(v, s, 64);
+        if (l == 0) dots[b] = v;
+    }
+    __syncthreads();
     if (t < 64) {
-        int idx = bucket_of(__ballot(t < kTau && part[t & (kTau - 1)][0] >= 0.f));
+        int idx = bucket_of(__ballot(t < kTau && dots[t & (kTau - 1)] >= 0.f));
         for (int k = 1; k < kHashLayers; ++k) {
             const uint32_t* y = tab + ((k - 1) * kDh + idx) * kDhWords;  // y_k = T_k[idx]
             int mismatch = 0;
