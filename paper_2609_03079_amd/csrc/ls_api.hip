@@ -44,6 +44,7 @@ struct ls_ffn {
     float* a = nullptr;       // [maxB, F]
     float* xbuf = nullptr;    // [maxB, d]  ping-pong partner of the decode step
     float* dn_part = nullptr; // [kDownPartsMax, maxB, d]  parts of the split down projection
+    uint8_t* split = nullptr; // inputs prepared by the selection launch of the decode step
     int64_t last_act_n = 0;
     int32_t last_act_B = 0;
     const float* last_act_src = nullptr;  // activations buffer of the last sparse step
@@ -300,7 +301,7 @@ void free_all(ls_ffn* c) {
     for (void* p : {(void*)c->z, (void*)c->scores, (void*)c->idx, (void*)c->count,
                     (void*)c->a, (void*)c->xbuf, (void*)c->dn_part, (void*)c->cache, (void*)c->slot_tables,
                     (void*)c->mailbox, (void*)c->layer_tab, (void*)c->dev_err, (void*)c->spec_idx,
-                    (void*)c->trace, (void*)c->stage_cnt})
+                    (void*)c->trace, (void*)c->stage_cnt, (void*)c->split})
         if (p) (void)hipFree(p);
     if (c->staging) (void)hipHostFree(c->staging);
     for (auto p : c->host_blocks) if (p) (void)hipHostFree(p);
@@ -482,7 +483,8 @@ ls_status ls_ffn_create(const ls_ffn_desc* desc, ls_ffn** out) {
         dmalloc(&c->scores, (size_t)B * s.n_blk) != hipSuccess ||
         dmalloc(&c->idx, (size_t)B * s.n_blk) != hipSuccess || dmalloc(&c->count, (size_t)B) != hipSuccess ||
         dmalloc(&c->a, (size_t)B * s.F) != hipSuccess || dmalloc(&c->xbuf, (size_t)B * s.d) != hipSuccess ||
-        dmalloc(&c->dn_part, (size_t)ls::kDownPartsMax * B * s.d) != hipSuccess) {
+        dmalloc(&c->dn_part, (size_t)ls::kDownPartsMax * B * s.d) != hipSuccess ||
+        (ls::split_bytes(s, B) > 0 && dmalloc(&c->split, ls::split_bytes(s, B)) != hipSuccess)) {
         (void)hipGetLastError();
         return bail(LS_E_NOMEM, "workspace allocation failed");
     }
@@ -654,7 +656,7 @@ ls_status ls_select_blocks(ls_ffn* c, const float* scores, int32_t B, ls_sel_mod
         return fail(c, LS_E_INVAL, "threshold selection needs cap >= n_blk");
     }
     LS_HIP(c, timed(c, LS_K_SELECT, [&] {
-        return ls::launch_select(scores, B, n, (int)mode, k, tau, union_batch ? 1 : 0, cap, idx, count, c->stream);
+        return ls::launch_select(scores, B, n, (int)mode, k, tau, union_batch ? 1 : 0, cap, idx, count, nullptr, c->stream);
     }));
     return LS_OK;
 }
@@ -700,7 +702,7 @@ static ls_status sparse_step(ls_ffn* c, int32_t layer, const float* x_in, int32_
         st = wait_stages(c, layer, begin, end);
         if (st != LS_OK) return st;
     }
-    auto gateup = [&] { return ls::launch_gateup(s, L, slot_table, x_in, B, idx, count, begin, end, a_buf, c->stream); };
+    auto gateup = [&] { return ls::launch_gateup(s, L, slot_table, x_in, B, idx, count, begin, end, a_buf, nullptr, c->stream); };
     auto down = [&] { return ls::launch_down(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, part, c->stream); };
     LS_HIP(c, may_time ? timed(c, LS_K_GATEUP, gateup) : gateup());
     LS_HIP(c, may_time ? timed(c, LS_K_DOWN, down) : down());
@@ -1170,12 +1172,15 @@ ls_status ls_decode_step(ls_ffn* c, float* x, int32_t B, int32_t k) {
                 return ls::launch_gateup_select(s, L, cur, c->scores, k, c->idx, c->count, c->a, c->stream);
             }));
         } else {
+            // the selection's launch also prepares the inputs of the gate/up kernels that take them so
+            ls::SplitJob job{};
+            const ls::SplitJob* pre = ls::split_job(s, B, cap, cur, c->split, &job) ? &job : nullptr;
             LS_HIP(c, timed(c, LS_K_SELECT, [&] {
-                return ls::launch_select(c->scores, B, s.n_blk, LS_SEL_TOPK, k, 0.f, 1, cap, c->idx, c->count,
+                return ls::launch_select(c->scores, B, s.n_blk, LS_SEL_TOPK, k, 0.f, 1, cap, c->idx, c->count, pre,
                                          c->stream);
             }));
             LS_HIP(c, timed(c, LS_K_GATEUP, [&] {
-                return ls::launch_gateup(s, L, nullptr, cur, B, c->idx, c->count, 0, cap, c->a, c->stream);
+                return ls::launch_gateup(s, L, nullptr, cur, B, c->idx, c->count, 0, cap, c->a, pre, c->stream);
             }));
         }
         LS_HIP(c, timed(c, LS_K_DOWN, [&] { return ls::launch_down(s, L, nullptr, c->a, B, c->idx, c->count, 0, cap, cur, nxt, c->dn_part, c->stream); }));

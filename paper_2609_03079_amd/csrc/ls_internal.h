@@ -85,14 +85,33 @@ struct HashDev {
 // scores[b, :] = the hashing predictor's block scores of token b of x [B, d]
 hipError_t launch_hash_predict(int d, int nblk, const float* x, int B, const HashDev& h, float* scores,
                                hipStream_t st);
+// Preparation of a batch's inputs for the resident matrix-core gate/up kernel: the fragments of
+// its slices and, per slice and slot, their scale and sum of squares (ls_split.h).
+constexpr int kSplitSlices = 8;  // slices of a row, at most
+struct SplitJob {
+    const float* x;  // [B, d]
+    float* meta;     // [2][kSplitSlices][8]: factors the parts were divided by, sums of squares
+    float* frag;     // [W][NK][fragments][64] 16-byte operands
+    int B, d, NK, W;
+    int bp;          // tokens padded: 2, 4 or 8
+    int bf16;
+};
+// Whether the gate/up launch of these arguments (a list of up to n entries) runs that kernel; then
+// the job that prepares it in buf (split_bytes; null: false).
+bool split_job(const Shape& s, int B, int n, const float* x, void* buf, SplitJob* job);
+size_t split_bytes(const Shape& s, int max_batch);
+// job: null, or inputs to prepare beside the selection, one more workgroup a slice (the
+// selection has one workgroup, whose time covers theirs)
 hipError_t launch_select(const float* scores, int B, int n_blk, int mode, int k, float tau,
-                         int union_batch, int cap, int32_t* idx, int32_t* count, hipStream_t st);
+                         int union_batch, int cap, int32_t* idx, int32_t* count, const SplitJob* job,
+                         hipStream_t st);
 // slot_table: null in resident mode (block b lives at blocks + b*block_bytes); else
 // device int32 [n_blk] giving the cache slot of block b, relative to `blocks`.
 // x: the layer input [B, d]; the RMS scale is applied when s.prenorm
+// job: null, or the prepared inputs (of the same x and list length)
 hipError_t launch_gateup(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                          const float* x, int B, const int32_t* idx, const int32_t* count,
-                         int begin, int end, float* a_buf, hipStream_t st);
+                         int begin, int end, float* a_buf, const SplitJob* job, hipStream_t st);
 // Batch 1, resident weights: the top-k selection of `scores` (as launch_select with
 // LS_SEL_TOPK, k, no union) and the gate/up gather of its list in one launch; writes idx[0..n)
 // and count[0] = n for launch_down.  gateup_select_ok: whether the shape allows it.
@@ -141,7 +160,7 @@ bool gateup_on_mfma(const Shape& s, int B, int n);
 bool down_on_mfma(const Shape& s, int B, int n);
 hipError_t launch_gateup_mfma(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                               const float* x, int B, const int32_t* idx, const int32_t* count,
-                              int begin, int end, float* a_buf, hipStream_t st);
+                              int begin, int end, float* a_buf, const SplitJob* job, hipStream_t st);
 constexpr int kDownPartsMax = 8;  // list parts of the matrix-core down projection, at most
 hipError_t launch_down_mfma(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                             const float* a_buf, int B, const int32_t* idx, const int32_t* count,

@@ -17,6 +17,7 @@
 #include "ls_device.h"
 #include "ls_internal.h"
 #include "ls_sparse.h"
+#include "ls_split.h"
 
 namespace ls {
 namespace {
@@ -249,7 +250,21 @@ __global__ __launch_bounds__(Q > 8 ? 512 : 1024) void select_kernel(const float*
                                                       int n, int mode, int k, float tau,
                                                       int union_batch, int cap,
                                                       int32_t* __restrict__ idx,
-                                                      int32_t* __restrict__ count) {
+                                                      int32_t* __restrict__ count, SplitJob job) {
+    if (blockIdx.x > 0) {  // the inputs of the next kernel, a slice per workgroup (its first wave)
+        if (threadIdx.x >= 64) return;
+        const int w = (int)blockIdx.x - 1, lane = threadIdx.x;
+        if (job.bf16) {
+            if (job.bp == 2) split_slice<LS_BF16, 2>(job, w, lane);
+            else if (job.bp == 4) split_slice<LS_BF16, 4>(job, w, lane);
+            else split_slice<LS_BF16, 8>(job, w, lane);
+        } else {
+            if (job.bp == 2) split_slice<LS_F16, 2>(job, w, lane);
+            else if (job.bp == 4) split_slice<LS_F16, 4>(job, w, lane);
+            else split_slice<LS_F16, 8>(job, w, lane);
+        }
+        return;
+    }
     // per token: its members' rank words; with a union, row 0 holds the union's instead
     __shared__ uint64_t mk[kMaxBatch][kMaxBlocks];
     __shared__ uint32_t bkey[kMaxBlocks];           // union: largest key of block i over all tokens
@@ -574,7 +589,8 @@ hipError_t launch_fold_predictor(ls_dtype t, const void* P1, const void* P2, int
 }
 
 hipError_t launch_select(const float* scores, int B, int n_blk, int mode, int k, float tau,
-                         int union_batch, int cap, int32_t* idx, int32_t* count, hipStream_t st) {
+                         int union_batch, int cap, int32_t* idx, int32_t* count, const SplitJob* job,
+                         hipStream_t st) {
     // one wave per token; more waves share the union ranking
     int waves = (n_blk + 63) / 64;
     waves = waves < B ? B : waves;
@@ -588,8 +604,8 @@ hipError_t launch_select(const float* scores, int B, int n_blk, int mode, int k,
               : n_blk <= 256 ? select_kernel<4>
               : n_blk <= 512 ? select_kernel<8>
                              : select_kernel<kMaxBlocks / 64>;
-    hipLaunchKernelGGL(fn, dim3(1), dim3(threads), 0, st, scores, B, n_blk, mode, k, tau,
-                       union_batch, cap, idx, count);
+    hipLaunchKernelGGL(fn, dim3(job ? 1 + job->W : 1), dim3(threads), 0, st, scores, B, n_blk, mode, k, tau,
+                       union_batch, cap, idx, count, job ? *job : SplitJob{});
     return hipGetLastError();
 }
 
@@ -662,9 +678,9 @@ static hipError_t gateup_t(const Shape& s, const LayerDev& L, const int32_t* slo
 
 hipError_t launch_gateup(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                          const float* h, int B, const int32_t* idx, const int32_t* count,
-                         int begin, int end, float* a_buf, hipStream_t st) {
+                         int begin, int end, float* a_buf, const SplitJob* job, hipStream_t st) {
     if (s.batch_mfma && !s.zero_skip && gateup_on_mfma(s, B, end - begin))
-        return launch_gateup_mfma(s, L, slot_table, h, B, idx, count, begin, end, a_buf, st);
+        return launch_gateup_mfma(s, L, slot_table, h, B, idx, count, begin, end, a_buf, job, st);
     const bool relu = s.act == LS_ACT_REGLU;
     switch (s.dtype) {
         case LS_F32:

@@ -15,6 +15,7 @@
 
 #include "ls_device.h"
 #include "ls_internal.h"
+#include "ls_split.h"
 
 namespace ls {
 namespace {
@@ -92,19 +93,6 @@ __device__ __forceinline__ f32x4 gload_x(const float* uniform_base, uint32_t byt
     return *(gf4_ptr)((const char*)(((uint64_t)hi << 32) | lo) + byte_off);
 }
 
-// sum of N (a power of two) values, pairwise
-template <int N>
-__device__ __forceinline__ float tree_sum(const float (&v)[N]) {
-    float t[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) t[i] = v[i];
-#pragma unroll
-    for (int n = N / 2; n > 0; n /= 2)
-#pragma unroll
-        for (int i = 0; i < n; ++i) t[i] += t[i + n];
-    return t[0];
-}
-
 // a barrier that orders LDS only: global loads already issued stay in flight
 __device__ __forceinline__ void lds_barrier_m() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -139,50 +127,18 @@ __device__ __forceinline__ void lds_barrier_m() {
 // Mistral-7B shape at B = 4 (105 blocks, 220 MB) 61.7 -> 41.6 us, 13B shape at B = 8 (138
 // blocks, 181 MB) 45.0 -> 37.2 us.  From 45 to 180 MB it reads 7.0 TB/s; about 8 us of a launch
 // are the list, the input's conversion and the last sums.
-constexpr int kGuWaves = 8;   // slices, at most
-
-// Parts of values, two at a time (a word holds the pair's 16-bit parts).  first(): the leading
-// part; v is left as the (scaled) remainder; a value that is not finite leaves none.
-template <ls_dtype T>
-struct Part;
-template <>
-struct Part<LS_F16> {
-    static constexpr int kParts = 2;
-    static constexpr int kShift = 11;  // the second part is scaled by 2^11
-    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-    __device__ static inline uint32_t pack(float a, float b) {
-        const f16x2 h = {(_Float16)a, (_Float16)b};
-        return __builtin_bit_cast(uint32_t, h);
-    }
-    __device__ static inline float rest(float v) {
-        const float r = (v - (float)(_Float16)v) * 2048.f;
-        return fabsf(v) < INFINITY ? r : 0.f;
-    }
-};
-template <>
-struct Part<LS_BF16> {
-    static constexpr int kParts = 3;   // 8 bits each, cut off: exact
-    static constexpr int kShift = 0;
-    // the upper halves of two values (a NaN stays one: its quiet bit is set)
-    __device__ static inline uint32_t pack(float a, float b) {
-        const uint32_t ua = __float_as_uint(a) | (a != a ? 0x400000u : 0u);
-        const uint32_t ub = __float_as_uint(b) | (b != b ? 0x400000u : 0u);
-        return (ua >> 16) | (ub & 0xffff0000u);
-    }
-    __device__ static inline float rest(float v) {
-        const float r = v - __uint_as_float(__float_as_uint(v) & 0xffff0000u);
-        return fabsf(v) < INFINITY ? r : 0.f;
-    }
-};
+constexpr int kGuWaves = kSplitSlices;  // slices, at most
 
 // FULL: every wave has NK steps (d / 64 = W NK); the addresses of a unit's loads then differ only in
-// their immediate offsets.
-template <ls_dtype T, int NK, int BP, bool FULL>
+// their immediate offsets.  PRE: the fragments (and the slices' scales and sums of squares) were
+// prepared by the selection launch (the same bits); the wave then only loads them.
+template <ls_dtype T, int NK, int BP, bool FULL, bool PRE>
 __global__ __launch_bounds__(64 * kGuWaves) void gateup_mfma_kernel(
     const uint8_t* __restrict__ blocks, size_t block_bytes, const int32_t* __restrict__ slot_table,
     const void* __restrict__ bias, float thresh, const float* __restrict__ x, int B, int d, int blk,
     int n_blk, int F, const int32_t* __restrict__ idx, const int32_t* __restrict__ count, int begin,
-    int end, float* __restrict__ a_buf, int reglu, int rms) {
+    int end, float* __restrict__ a_buf, int reglu, int rms, const u32x4* __restrict__ frag,
+    const float* __restrict__ meta) {
     using S = Split<T>;
     typedef typename S::vec vec;
     constexpr int P = Part<T>::kParts;
@@ -209,8 +165,18 @@ __global__ __launch_bounds__(64 * kGuWaves) void gateup_mfma_kernel(
     // past the slice its first
     const int tok = (lane & 7) & (BP - 1);
     const int half = (lane >> 3) & 1;
-    f32x4 xv[NK][2];
-    {
+    f32x4 xv[PRE ? 1 : NK][2];
+    u32x4 pre[PRE ? NF : 1][PRE ? NK : 1];
+    float pre_unscale = 1.f, pre_ss = 0.f;
+    if constexpr (PRE) {
+        const u32x4* src = frag + (size_t)wave * NK * NF * 64;
+#pragma unroll
+        for (int s = 0; s < NK; ++s)
+#pragma unroll
+            for (int f = 0; f < NF; ++f) pre[f][s] = src[(s * NF + f) * 64 + lane];
+        pre_unscale = meta[wave * 8 + (lane & 7)];
+        pre_ss = meta[kSplitSlices * 8 + wave * 8 + (lane & 7)];
+    } else {
         const uint32_t xo = ((uint32_t)(tok < B ? tok : 0) * (uint32_t)d + 16u * (uint32_t)(lane >> 4) + 8u * (uint32_t)half) * 4u;
         const float* xs = x + (size_t)s0 * 64;
 #pragma unroll
@@ -251,7 +217,14 @@ __global__ __launch_bounds__(64 * kGuWaves) void gateup_mfma_kernel(
     // x into parts
     vec xf[NF][NK];
     float unscale = 1.f;
-    {
+    if constexpr (PRE) {
+#pragma unroll
+        for (int s = 0; s < NK; ++s)
+#pragma unroll
+            for (int f = 0; f < NF; ++f) xf[f][s] = S::from_raw(pre[f][s]);
+        unscale = pre_unscale;
+        if (lane < 8) pss[wave][lane] = pre_ss;
+    } else {
         float s4[4], mx = 0.f;  // four short chains: the scale's error goes into every sum
 #pragma unroll
         for (int i = 0; i < 4; ++i) s4[i] = 0.f;
@@ -268,40 +241,12 @@ __global__ __launch_bounds__(64 * kGuWaves) void gateup_mfma_kernel(
 #pragma unroll
             for (int off = 8; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
         }
-        int ex = 0;
-        if (T == LS_F16 && mx > 0.f) {
-            ex = (int)((__float_as_uint(mx) >> 23) & 0xffu) - 127;  // a subnormal maximum: -127
-            unscale = ldexpf(1.f, ex);
-        }
+        const int ex = T == LS_F16 ? split_exponent(mx) : 0;
+        unscale = ldexpf(1.f, ex);
 #pragma unroll
         for (int s = 0; s < NK; ++s) {
             u32x4 words[NF];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                float v0 = xv[s][j >> 1][(2 * j) & 3], v1 = xv[s][j >> 1][(2 * j + 1) & 3];
-                s4[(2 * j) & 3] = fmaf(v0, v0, s4[(2 * j) & 3]);
-                s4[(2 * j + 1) & 3] = fmaf(v1, v1, s4[(2 * j + 1) & 3]);
-                if (T == LS_F16) v0 = ldexpf(v0, -ex), v1 = ldexpf(v1, -ex);
-                // slot q of fragment f is part (8 f + q) / BP
-                float p0[P], p1[P];
-#pragma unroll
-                for (int p = 0; p < P; ++p) {
-                    p0[p] = v0;
-                    p1[p] = v1;
-                    if (p + 1 < P) v0 = Part<T>::rest(v0), v1 = Part<T>::rest(v1);
-                }
-#pragma unroll
-                for (int f = 0; f < NF; ++f) {
-                    float a = p0[f * 8 / BP], b = p1[f * 8 / BP];
-#pragma unroll
-                    for (int p = f * 8 / BP + 1; p < P && p * BP < f * 8 + 8; ++p) {
-                        const bool mine = (lane & 7) >= p * BP - f * 8;
-                        a = mine ? p0[p] : a;
-                        b = mine ? p1[p] : b;
-                    }
-                    words[f][j] = Part<T>::pack(a, b);
-                }
-            }
+            split_step<T, BP>(xv[s], ex, lane, s4, words);
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
                 asm volatile("" : "+v"(words[f]));
@@ -927,32 +872,44 @@ bool down_on_mfma(const Shape& s, int B, int n) {
     return mfma_shape(s, B) && (B >= 4 || 2.0 * n * s.blk * s.d >= (B == 2 ? 60e6 : 32e6));
 }
 
+// Steps of the shortest slice that eight waves or fewer cover a row with (0: none does).
+static int slice_steps(int d) {
+    for (int nk : {4, 6, 8, 10, 12, 16})
+        if (d <= 64 * nk * kGuWaves) return nk;
+    return 0;
+}
+
 template <ls_dtype T, int BP>
 static hipError_t gateup_resident_bp(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* x, int B,
                                      const int32_t* idx, const int32_t* count, int begin, int end, float* a_buf,
-                                     hipStream_t st) {
+                                     const SplitJob* job, hipStream_t st) {
     const size_t bb = s.block_elems * elem_size(s.dtype);
     const int steps = s.d / 64;
     const long groups = (long)(end - begin) * (s.blk / 8);
     const int cus = std::max(1, cu_count());
-#define LS_GUR_K(NK, FULL)                                                                                             \
-    hipLaunchKernelGGL((gateup_mfma_kernel<T, NK, BP, FULL>), dim3((unsigned)grid), dim3(64 * W), 0, st, L.blocks,  \
+#define LS_GUR_K(NK, FULL, PRE)                                                                                        \
+    hipLaunchKernelGGL((gateup_mfma_kernel<T, NK, BP, FULL, PRE>), dim3((unsigned)grid), dim3(64 * W), 0, st, L.blocks,  \
                        bb, slot_table, L.bias, L.threshold, x, B, s.d, s.blk, s.n_blk, s.F, idx, count, begin, end,    \
-                       a_buf, s.act == LS_ACT_REGLU ? 1 : 0, s.prenorm)
+                       a_buf, s.act == LS_ACT_REGLU ? 1 : 0, s.prenorm, reinterpret_cast<const u32x4*>(job ? job->frag : nullptr),      \
+                       job ? job->meta : nullptr)
 #define LS_GUR(NK)                                                                                                     \
     do {                                                                                                               \
         const int W = (steps + NK - 1) / NK;                                                                           \
         const long grid = std::min<long>(groups, (long)cus * std::max(1, kGuWaves / W));                               \
-        if (steps == W * NK) LS_GUR_K(NK, true); else LS_GUR_K(NK, false);                                             \
+        if (steps == W * NK) { if (job) LS_GUR_K(NK, true, true); else LS_GUR_K(NK, true, false); }                    \
+        else { if (job) LS_GUR_K(NK, false, true); else LS_GUR_K(NK, false, false); }                                  \
     } while (0)
-    // the shortest slice that eight waves or fewer cover the row with
-    if (steps <= 4 * kGuWaves) LS_GUR(4);
-    else if (steps <= 6 * kGuWaves) LS_GUR(6);
-    else if (steps <= 8 * kGuWaves) LS_GUR(8);
-    else if (steps <= 10 * kGuWaves) LS_GUR(10);
-    else if (steps <= 12 * kGuWaves) LS_GUR(12);
-    else if constexpr (T == LS_F16 || BP <= 4) LS_GUR(16);
-    else return hipErrorInvalidValue;
+    switch (slice_steps(s.d)) {
+        case 4: LS_GUR(4); break;
+        case 6: LS_GUR(6); break;
+        case 8: LS_GUR(8); break;
+        case 10: LS_GUR(10); break;
+        case 12: LS_GUR(12); break;
+        case 16:
+            if constexpr (T == LS_F16 || BP <= 4) { LS_GUR(16); break; }
+            return hipErrorInvalidValue;
+        default: return hipErrorInvalidValue;
+    }
 #undef LS_GUR
 #undef LS_GUR_K
     return hipGetLastError();
@@ -961,19 +918,43 @@ static hipError_t gateup_resident_bp(const Shape& s, const LayerDev& L, const in
 template <ls_dtype T>
 static hipError_t gateup_resident_t(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* x, int B,
                                     const int32_t* idx, const int32_t* count, int begin, int end, float* a_buf,
-                                    hipStream_t st) {
-    if (B <= 2) return gateup_resident_bp<T, 2>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, st);
-    if (B <= 4) return gateup_resident_bp<T, 4>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, st);
-    return gateup_resident_bp<T, 8>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, st);
+                                    const SplitJob* job, hipStream_t st) {
+    if (B <= 2) return gateup_resident_bp<T, 2>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st);
+    if (B <= 4) return gateup_resident_bp<T, 4>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st);
+    return gateup_resident_bp<T, 8>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st);
+}
+
+bool split_job(const Shape& s, int B, int n, const float* x, void* buf, SplitJob* job) {
+    if (!buf || !s.batch_mfma || s.zero_skip || !gateup_on_mfma(s, B, n) || keeps_order(s, B) || !resident_ok(s, B))
+        return false;
+    const int NK = slice_steps(s.d), W = (s.d / 64 + NK - 1) / NK;
+    job->x = x;
+    job->meta = static_cast<float*>(buf);
+    job->frag = job->meta + 2 * 8 * kSplitSlices;
+    job->B = B;
+    job->d = s.d;
+    job->NK = NK;
+    job->W = W;
+    job->bp = B <= 2 ? 2 : (B <= 4 ? 4 : 8);
+    job->bf16 = s.dtype == LS_BF16;
+    return true;
+}
+
+size_t split_bytes(const Shape& s, int max_batch) {
+    if (s.dtype == LS_F32 || max_batch < kMfmaMinBatch) return 0;
+    const int NK = slice_steps(s.d);
+    if (!NK) return 0;
+    const size_t W = (size_t)(s.d / 64 + NK - 1) / NK;
+    return 2 * 8 * kSplitSlices * sizeof(float) + W * NK * 3 * 1024;  // up to three fragments
 }
 
 hipError_t launch_gateup_mfma(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                               const float* x, int B, const int32_t* idx, const int32_t* count,
-                              int begin, int end, float* a_buf, hipStream_t st) {
+                              int begin, int end, float* a_buf, const SplitJob* job, hipStream_t st) {
     if (end <= begin) return hipSuccess;
     if (!keeps_order(s, B) && resident_ok(s, B)) {
-        return s.dtype == LS_F16 ? gateup_resident_t<LS_F16>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, st)
-                                 : gateup_resident_t<LS_BF16>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, st);
+        return s.dtype == LS_F16 ? gateup_resident_t<LS_F16>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st)
+                                 : gateup_resident_t<LS_BF16>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st);
     }
     const long groups = (long)(end - begin) * (s.blk / 16);
     const size_t bb = s.block_elems * elem_size(s.dtype);

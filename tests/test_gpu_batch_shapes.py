@@ -119,3 +119,35 @@ def test_batched_inputs_beyond_float16():
         # d = 1024), taken over the largest activation
         assert np.max(np.abs(a[b] - ref[b])) <= 2e-5 * max(np.max(np.abs(ref[b])), 1e-30), b
     f.close()
+
+
+@pytest.mark.parametrize("dtype", [lsgen.DT_F16, lsgen.DT_BF16])
+@pytest.mark.parametrize("d,B", [(64, 4), (448, 8), (2880, 5), (4096, 4), (5120, 8), (6144, 6), (4096, 3)])
+def test_decode_step_prepares_the_same_inputs(d, B, dtype):
+    """The decode step's selection launch prepares the gate/up kernel's inputs; the separate calls'
+    gate/up prepares its own: the same bits, also for infinite, tiny and zero tokens."""
+    # (3 tokens take the matrix cores from 30 MB of gate/up rows on)
+    cfg = lsgen.CONFIGS["llama2_7b_ffn"].with_(n_layers=2, d_model=d, d_ff=1024 if B != 3 else 8192, block=32, rank=64,
+                                               dtype=dtype, prenorm=d != 448)
+    f, _ = make_ffn(cfg, max_batch=B)
+    f.ls_configure(lsffn.LS_CFG_DECODE_PATH, 1)
+    xs = lsgen.tokens(cfg, 3, 1, B)[0]
+    xs[1] *= np.float32(1e-6)
+    xs[2] = 0
+    if B > 4:
+        xs[4, ::7] = np.inf
+    nb, k = cfg.n_blk, cfg.n_blk // 2
+    cap = min(nb, B * k)
+    x, out = dev_f32(xs), empty_f32(B, d)
+    scores = empty_f32(B, nb)
+    idx = torch.zeros(cap, dtype=torch.int32, device="cuda")
+    cnt = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for l in range(cfg.n_layers):
+        f.ls_predict(l, x, B, scores)
+        f.ls_select_blocks(scores, B, lsffn.LS_SEL_TOPK, k, 0.0, 1, cap, idx, cnt)
+        f.ls_sparse_ffn_step(l, x, B, idx, cnt, 0, cap, out)
+        x, out = out, x
+    y = dev_f32(xs)
+    f.ls_decode_step(y, B, k)
+    assert np.array_equal(host(y), host(x), equal_nan=True)
+    f.close()
