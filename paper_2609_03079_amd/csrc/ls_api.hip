@@ -44,6 +44,7 @@ struct ls_ffn {
     float* a = nullptr;       // [maxB, F]
     float* xbuf = nullptr;    // [maxB, d]  ping-pong partner of the decode step
     float* dn_part = nullptr; // [kDownPartsMax, maxB, d]  parts of the split down projection
+    uint32_t* dn_cnt = nullptr; // [d / kColTile]  its workgroups done per column group (zero between calls)
     uint8_t* split = nullptr; // inputs prepared by the selection launch of the decode step
     int64_t last_act_n = 0;
     int32_t last_act_B = 0;
@@ -301,7 +302,7 @@ void free_all(ls_ffn* c) {
     for (void* p : {(void*)c->z, (void*)c->scores, (void*)c->idx, (void*)c->count,
                     (void*)c->a, (void*)c->xbuf, (void*)c->dn_part, (void*)c->cache, (void*)c->slot_tables,
                     (void*)c->mailbox, (void*)c->layer_tab, (void*)c->dev_err, (void*)c->spec_idx,
-                    (void*)c->trace, (void*)c->stage_cnt, (void*)c->split})
+                    (void*)c->trace, (void*)c->stage_cnt, (void*)c->split, (void*)c->dn_cnt})
         if (p) (void)hipFree(p);
     if (c->staging) (void)hipHostFree(c->staging);
     for (auto p : c->host_blocks) if (p) (void)hipHostFree(p);
@@ -484,6 +485,7 @@ ls_status ls_ffn_create(const ls_ffn_desc* desc, ls_ffn** out) {
         dmalloc(&c->idx, (size_t)B * s.n_blk) != hipSuccess || dmalloc(&c->count, (size_t)B) != hipSuccess ||
         dmalloc(&c->a, (size_t)B * s.F) != hipSuccess || dmalloc(&c->xbuf, (size_t)B * s.d) != hipSuccess ||
         dmalloc(&c->dn_part, (size_t)ls::kDownPartsMax * B * s.d) != hipSuccess ||
+        dmalloc(&c->dn_cnt, (size_t)(s.d / ls::kColTile)) != hipSuccess ||
         (ls::split_bytes(s, B) > 0 && dmalloc(&c->split, ls::split_bytes(s, B)) != hipSuccess)) {
         (void)hipGetLastError();
         return bail(LS_E_NOMEM, "workspace allocation failed");
@@ -497,6 +499,7 @@ ls_status ls_ffn_create(const ls_ffn_desc* desc, ls_ffn** out) {
             return bail(LS_E_NOMEM, "fused-kernel workspace allocation failed");
         }
         if (hipMemset(c->mailbox, 0, c->mailbox_words * sizeof(uint64_t)) != hipSuccess ||
+            hipMemset(c->dn_cnt, 0, (size_t)(s.d / ls::kColTile) * sizeof(uint32_t)) != hipSuccess ||
             empty_bare_words(c) != hipSuccess ||
             hipMemset(c->dev_err, 0, sizeof(int)) != hipSuccess ||
             hipMemset(c->layer_tab, 0, (size_t)L * sizeof(ls::LayerPtrs)) != hipSuccess)
@@ -703,7 +706,7 @@ static ls_status sparse_step(ls_ffn* c, int32_t layer, const float* x_in, int32_
         if (st != LS_OK) return st;
     }
     auto gateup = [&] { return ls::launch_gateup(s, L, slot_table, x_in, B, idx, count, begin, end, a_buf, nullptr, c->stream); };
-    auto down = [&] { return ls::launch_down(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, part, c->stream); };
+    auto down = [&] { return ls::launch_down(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, part, c->dn_cnt, c->stream); };
     LS_HIP(c, may_time ? timed(c, LS_K_GATEUP, gateup) : gateup());
     LS_HIP(c, may_time ? timed(c, LS_K_DOWN, down) : down());
     if (c->desc.residency == LS_WEIGHTS_HOST) {
@@ -1183,7 +1186,7 @@ ls_status ls_decode_step(ls_ffn* c, float* x, int32_t B, int32_t k) {
                 return ls::launch_gateup(s, L, nullptr, cur, B, c->idx, c->count, 0, cap, c->a, pre, c->stream);
             }));
         }
-        LS_HIP(c, timed(c, LS_K_DOWN, [&] { return ls::launch_down(s, L, nullptr, c->a, B, c->idx, c->count, 0, cap, cur, nxt, c->dn_part, c->stream); }));
+        LS_HIP(c, timed(c, LS_K_DOWN, [&] { return ls::launch_down(s, L, nullptr, c->a, B, c->idx, c->count, 0, cap, cur, nxt, c->dn_part, c->dn_cnt, c->stream); }));
         std::swap(cur, nxt);
     }
     if (cur != x)

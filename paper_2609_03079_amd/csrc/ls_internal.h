@@ -119,11 +119,11 @@ bool gateup_select_ok(const Shape& s, int B, int k);
 hipError_t launch_gateup_select(const Shape& s, const LayerDev& L, const float* x, const float* scores, int k,
                                 int32_t* idx, int32_t* count, float* a_buf, hipStream_t st);
 // part: [kDownPartsMax, B, d] floats of scratch for the matrix-core path's split list (may be
-// null: no split)
+// null: no split); cnt: d / kColTile words, zero between calls
 hipError_t launch_down(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                        const float* a_buf, int B, const int32_t* idx, const int32_t* count,
                        int begin, int end, const float* x_in, float* x_acc, float* part,
-                       hipStream_t st);
+                       uint32_t* cnt, hipStream_t st);
 
 // Streaming read of `bytes` (a multiple of 16) at buf by `grid` workgroups of 256 threads;
 // out: 4 * grid words of scratch.
@@ -165,6 +165,6 @@ constexpr int kDownPartsMax = 8;  // list parts of the matrix-core down projecti
 hipError_t launch_down_mfma(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                             const float* a_buf, int B, const int32_t* idx, const int32_t* count,
                             int begin, int end, const float* x_in, float* x_acc, float* part,
-                            hipStream_t st);
+                            uint32_t* cnt, hipStream_t st);
 
 }  // namespace ls

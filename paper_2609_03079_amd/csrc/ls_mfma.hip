@@ -521,6 +521,38 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(kGu
     }
 }
 
+// The last of the `splits` workgroups of a column group to store its part adds the parts in order of
+// part and writes x_acc, instead of one more launch (13B shape at B = 8, three layers 209 -> 206 us;
+// 2880 x 7720 at B = 5, one layer 37.6 -> 35.4).  Parts travel as agent-scope atomic words, coherent across the XCDs' L2s without cache
+// maintenance; a workgroup counts itself once its stores are complete, so whoever counts last
+// sees every part.  Nothing waits; the count is left at zero for the next call.
+// m(q): the index of the workgroup's q-th output in [B, d]; n outputs, B d apart per part.
+template <typename Index>
+__device__ __forceinline__ void finish_parts(const float* part, int splits, size_t stride, int n, Index m,
+                                             const float* __restrict__ x_in, float* x_acc, bool first, uint32_t* cnt) {
+    __shared__ uint32_t arrived;
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's part words are stored
+    __syncthreads();
+    if (threadIdx.x == 0) arrived = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (arrived != (uint32_t)splits - 1u) return;
+    if (threadIdx.x == 0) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int q = (int)threadIdx.x; q < n; q += (int)blockDim.x) {
+        const size_t i = m(q);
+        const float x = first ? x_in[i] : x_acc[i];
+        float v[kDownPartsMax];
+#pragma unroll
+        for (int p = 0; p < kDownPartsMax; ++p)
+            v[p] = p < splits ? __hip_atomic_load(part + (size_t)p * stride + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                              : 0.f;
+        float y = 0.f;
+#pragma unroll
+        for (int p = 0; p < kDownPartsMax; ++p)
+            if (p < splits) y += v[p];
+        x_acc[i] = x + y;
+    }
+}
+
 constexpr int kWavesDn = 16;  // down: waves per workgroup
 constexpr int kDnTiles = 4;   // down: 16-column tiles per workgroup, at most (d is a multiple of 64)
 
@@ -533,7 +565,7 @@ constexpr int kDnTiles = 4;   // down: 16-column tiles per workgroup, at most (d
 // and any block size works), for every tile of the workgroup: a wave loads the item's activations
 // once for NT weight fragments.  Those reads come from L2 but through the same per-CU path
 // as the weights, which bounds these kernels: at 8 tokens they are a quarter of the weights'
-// bytes at 4 tiles, and half at 2.  With the finish launch, 13B shape at B = 8 (138 blocks, 91
+// bytes at 4 tiles, and half at 2.  With the sum over parts, 13B shape at B = 8 (138 blocks, 91
 // MB) 24.2 -> 20.5 us, Mistral-7B shape at B = 4 with a ReLU gate (105 blocks, 110 MB) 31.8 ->
 // 24 us against two tiles and eight parts.
 //
@@ -544,15 +576,15 @@ constexpr int kDnTiles = 4;   // down: 16-column tiles per workgroup, at most (d
 // part by 2^11.  Two items are in flight per wave.
 //
 // With splits > 1 the list range is cut into `splits` equal parts (workgroup group + n_groups *
-// part); each part's sum goes to part_out[part][token][column] and down_finish_kernel adds the
-// parts in order.
+// part); each part's sum goes to part_out[part][token][column] and finish_parts adds the parts
+// in order.
 template <ls_dtype T, int BP, int NT>
 __global__ __launch_bounds__(64 * kWavesDn) void down_mfma_kernel(
     const uint8_t* __restrict__ blocks, size_t block_bytes, const int32_t* __restrict__ slot_table,
     const float* __restrict__ a_buf, int B, int F, int d, int blk, int n_blk,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ count, int begin, int end,
     const float* __restrict__ x_in, float* __restrict__ x_acc, int splits,
-    float* __restrict__ part_out, uint32_t cpe_magic) {
+    float* __restrict__ part_out, uint32_t* __restrict__ cnt, uint32_t cpe_magic) {
     using S = Split<T>;
     typedef typename S::vec vec;
     constexpr int P = Part<T>::kParts;
@@ -712,8 +744,12 @@ __global__ __launch_bounds__(64 * kWavesDn) void down_mfma_kernel(
         if (splits == 1)
             x_acc[m] = (begin == 0 ? x_in[m] : x_acc[m]) + y;
         else
-            part_out[(size_t)sp * B * d + m] = y;
+            __hip_atomic_store(part_out + (size_t)sp * B * d + m, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    if (splits > 1)
+        finish_parts(part_out, splits, (size_t)B * d, NT * 16 * B,
+                     [&](int q) { return (size_t)(q / (16 * NT)) * d + (size_t)grp * NT * kColTile + q % (16 * NT); },
+                     x_in, x_acc, begin == 0, cnt + grp);
 }
 
 // The batched down projection of thresholded gates (keeps_order below): one workgroup per NT
@@ -726,7 +762,7 @@ __global__ __launch_bounds__(64 * kWavesDn) void down_mfma_kernel(
 // With splits > 1 the list range is cut into `splits` equal parts (workgroup
 // tile + n_tiles * part) so that the workgroup count is a multiple of the CU count even when
 // the tile count is not; each part's sum goes to part_out[part][token][column] and
-// down_finish_kernel adds the parts in order.  The wave count is blockDim.x / 64 (at most
+// finish_parts adds the parts in order.  The wave count is blockDim.x / 64 (at most
 // kWavesDn, and at most kWavesDn / NT with NT > 1).
 template <ls_dtype T, int NT, int KU>
 __global__ __launch_bounds__(64 * kWavesDn) void down_ordered_kernel(
@@ -734,7 +770,7 @@ __global__ __launch_bounds__(64 * kWavesDn) void down_ordered_kernel(
     const float* __restrict__ a_buf, int B, int F, int d, int blk, int n_blk,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ count, int begin, int end,
     const float* __restrict__ x_in, float* __restrict__ x_acc, int splits,
-    float* __restrict__ part_out) {
+    float* __restrict__ part_out, uint32_t* __restrict__ cnt) {
     using S = Split<T>;
     constexpr int kU = KU;
     const int n_tiles = d / (kColTile * NT);
@@ -817,26 +853,12 @@ __global__ __launch_bounds__(64 * kWavesDn) void down_ordered_kernel(
         if (splits == 1)
             x_acc[m] = (begin == 0 ? x_in[m] : x_acc[m]) + y;
         else
-            part_out[(size_t)sp * B * d + m] = y;
+            __hip_atomic_store(part_out + (size_t)sp * B * d + m, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-}
-
-// x_acc[m] = (x_in or x_acc)[m] + the parts' sums for m in order of part; every load is issued
-// before the first sum (one round trip instead of one per part)
-template <int SP>
-__global__ __launch_bounds__(256) void down_finish_kernel(const float* __restrict__ part, int n,
-                                                          const float* __restrict__ x_in,
-                                                          float* __restrict__ x_acc, int first) {
-    const int m = (int)blockIdx.x * 256 + (int)threadIdx.x;
-    if (m >= n) return;
-    const float x = first ? x_in[m] : x_acc[m];
-    float v[SP];
-#pragma unroll
-    for (int p = 0; p < SP; ++p) v[p] = part[(size_t)p * n + m];
-    float y = 0.f;
-#pragma unroll
-    for (int p = 0; p < SP; ++p) y += v[p];
-    x_acc[m] = x + y;
+    if (splits > 1)
+        finish_parts(part_out, splits, (size_t)B * d, NT * 16 * B,
+                     [&](int q) { return (size_t)(q / (16 * NT)) * d + (size_t)tile * NT * kColTile + q % (16 * NT); },
+                     x_in, x_acc, begin == 0, cnt + tile);
 }
 
 }  // namespace
@@ -993,17 +1015,17 @@ static int down_splits(const Shape& s) {
 template <ls_dtype T, int BP, int NT>
 static void down_mfma_nt(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* a_buf, int B,
                          const int32_t* idx, const int32_t* count, int begin, int end, const float* x_in, float* x_acc,
-                         int splits, float* part, hipStream_t st) {
+                         int splits, float* part, uint32_t* cnt, hipStream_t st) {
     const size_t bb = s.block_elems * elem_size(s.dtype);
     const uint32_t cpe = (uint32_t)s.blk / 8u;
     const bool exact = cpe > 1 && (uint64_t)(s.F / 8) * cpe < (1ull << 32);
     const uint32_t magic = exact ? 0xffffffffu / cpe + 1u : 0u;
     hipLaunchKernelGGL((down_mfma_kernel<T, BP, NT>), dim3((unsigned)(s.d / (kColTile * NT) * splits)),
                        dim3(64 * kWavesDn), 0, st, L.blocks, bb, slot_table, a_buf, B, s.F, s.d, s.blk, s.n_blk, idx,
-                       count, begin, end, x_in, x_acc, splits, part, magic);
+                       count, begin, end, x_in, x_acc, splits, part, cnt, magic);
 }
 
-// One tile per workgroup and the whole list needs no finish launch (about 2.5 us) but reads and
+// One tile per workgroup and the whole list needs no sum over parts (2 to 3 us) but reads and
 // splits the activations once per 16 columns instead of once per 64, and its 16 waves leave room
 // for one workgroup per compute unit.  Measured at the longest list the call allows: d = 4096,
 // B = 4: 5 MB of weights 7.4 us against 9.0 with four tiles, 22 MB 12.1 / 12.0, 45 MB 15.1 / 15.4;
@@ -1016,21 +1038,20 @@ static bool down_one_tile(const Shape& s, int B, int n) {
 template <ls_dtype T, int BP>
 static void down_mfma_bp(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* a_buf, int B,
                          const int32_t* idx, const int32_t* count, int begin, int end, const float* x_in, float* x_acc,
-                         int splits, float* part, bool one, hipStream_t st) {
+                         int splits, float* part, uint32_t* cnt, bool one, hipStream_t st) {
     if (one)
-        down_mfma_nt<T, BP, 1>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, 1, part, st);
+        down_mfma_nt<T, BP, 1>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, 1, part, cnt, st);
     else
-        down_mfma_nt<T, BP, kDnTiles>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, st);
+        down_mfma_nt<T, BP, kDnTiles>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, cnt, st);
 }
 
 // The order of a thresholded gate's down projection: list parts and waves by shape (tiles that
 // do not fill whole rounds of the CUs and 128-row blocks take 8 parts of 4 waves, 64-row blocks
-// at B = 8 2 parts of 8, the rest one part of 16); the tiles per workgroup are free.  Returns the
-// number of parts.
+// at B = 8 2 parts of 8, the rest one part of 16); the tiles per workgroup are free.
 template <ls_dtype T>
-static int down_ordered_t(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* a_buf, int B,
+static void down_ordered_t(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* a_buf, int B,
                           const int32_t* idx, const int32_t* count, int begin, int end, const float* x_in,
-                          float* x_acc, float* part, hipStream_t st) {
+                          float* x_acc, float* part, uint32_t* cnt, hipStream_t st) {
     const size_t bb = s.block_elems * elem_size(s.dtype);
     const int cus = cu_count() > 0 ? cu_count() : 256;
     int splits = 1, waves = kWavesDn;
@@ -1041,42 +1062,31 @@ static int down_ordered_t(const Shape& s, const LayerDev& L, const int32_t* slot
 #define LS_DNO(NT, KU)                                                                                                 \
     hipLaunchKernelGGL((down_ordered_kernel<T, NT, KU>), dim3((unsigned)(s.d / (kColTile * NT) * splits)),             \
                        dim3(64 * waves), 0, st, L.blocks, bb, slot_table, a_buf, B, s.F, s.d, s.blk, s.n_blk, idx,     \
-                       count, begin, end, x_in, x_acc, splits, part)
+                       count, begin, end, x_in, x_acc, splits, part, cnt)
     if (splits == 8) LS_DNO(4, 2);
     else if (splits == 2) LS_DNO(2, 4);
     else LS_DNO(1, 2);
 #undef LS_DNO
-    return splits;
 }
 
 hipError_t launch_down_mfma(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                             const float* a_buf, int B, const int32_t* idx, const int32_t* count,
                             int begin, int end, const float* x_in, float* x_acc, float* part,
-                            hipStream_t st) {
+                            uint32_t* cnt, hipStream_t st) {
     const bool one = down_one_tile(s, B, end - begin);
-    int splits = part && !one ? down_splits(s) : 1;
-    if (keeps_order(s, B))
-        splits = s.dtype == LS_F16 ? down_ordered_t<LS_F16>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, part, st)
-                                   : down_ordered_t<LS_BF16>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, part, st);
+    const int splits = part && !one ? down_splits(s) : 1;
+    if (keeps_order(s, B) && s.dtype == LS_F16)
+        down_ordered_t<LS_F16>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, part, cnt, st);
+    else if (keeps_order(s, B) && s.dtype == LS_BF16)
+        down_ordered_t<LS_BF16>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, part, cnt, st);
     else if (s.dtype == LS_F16)
-        down_mfma_bp<LS_F16, 8>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, one, st);
+        down_mfma_bp<LS_F16, 8>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, cnt, one, st);
     else if (s.dtype == LS_BF16 && B <= 4)
-        down_mfma_bp<LS_BF16, 4>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, one, st);
+        down_mfma_bp<LS_BF16, 4>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, cnt, one, st);
     else if (s.dtype == LS_BF16)
-        down_mfma_bp<LS_BF16, 8>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, one, st);
+        down_mfma_bp<LS_BF16, 8>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, cnt, one, st);
     else
         return hipErrorInvalidValue;
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || splits == 1) return e;
-    const int n = B * s.d, first = begin == 0 ? 1 : 0;
-    const dim3 grid((unsigned)((n + 255) / 256)), blk(256);
-    switch (splits) {
-#define LS_FIN(SP) case SP: hipLaunchKernelGGL(down_finish_kernel<SP>, grid, blk, 0, st, part, n, x_in, x_acc, first); break
-        LS_FIN(2); LS_FIN(3); LS_FIN(4); LS_FIN(5); LS_FIN(6); LS_FIN(7); LS_FIN(8);
-#undef LS_FIN
-        default: return hipErrorInvalidValue;
-    }
-    static_assert(kDownPartsMax == 8, "a finish kernel per number of parts");
     return hipGetLastError();
 }
 
