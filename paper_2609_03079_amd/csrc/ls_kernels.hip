@@ -55,7 +55,7 @@ __global__ __launch_bounds__(64 * NW) void gemv_rows_kernel(const uint8_t* __res
     // PRE: the input chunks are requested with the weights, so the products wait for one round
     // trip; where they would take more than 32 registers of 16 bytes each chunk's input read is
     // issued at its first use
-    constexpr bool PRE = U * B * (V / 4) <= 32;
+    constexpr bool PRE = (R == 1 || B <= 3) && U * B * (V / 4) <= 32;
     constexpr int UX = PRE ? U : 1;
     for (int c0 = threadIdx.x; c0 < nchunk; c0 += 64 * NW * U) {
         u32x4 raw[U][R];
@@ -489,21 +489,26 @@ hipError_t launch_gateup_select(const Shape& s, const LayerDev& L, const float* 
 template <ls_dtype T, bool RMS>
 static hipError_t gemv_t(const void* W, int rows, int cols, int G, int rpw, const float* v, int B,
                          float* out, hipStream_t st) {
-    // one row per workgroup (four at B >= 4 had left most compute units without one), on four
+    // one row per workgroup (four at B >= 4 leave compute units without one: 216 rows of 5120 at
+    // B = 8 8.2 -> 5.8 us), from four rows per compute unit on four at B >= 4 (they share the
+    // input reads, B times a row's bytes, which dominate there), on four
     // waves at B = 2, 3 and eight otherwise (B = 1 against four: 7B shape 1664 -> 1681 tokens/s,
     // 13B 1106 -> 1114 on the per-kernel path)
     const int NW = B == 2 || B == 3 ? 4 : 8;
-    const dim3 grid((unsigned)rows), blk(64 * NW);
+    const bool four = B >= 4 && rows >= 4 * cu_count();
+    const dim3 grid((unsigned)(four ? (rows + 3) / 4 : rows)), blk(64 * NW);
     const uint8_t* w = static_cast<const uint8_t*>(W);
     const int per_lane = (cols / Wt<T>::V + 64 * NW - 1) / (64 * NW);
-#define LS_GEMV_U(NB, NWV, U) hipLaunchKernelGGL((gemv_rows_kernel<T, NB, RMS, 1, NWV, U>), grid, blk, 0, st, w, rows, cols, G, rpw, v, out)
+#define LS_GEMV_R(NB, R, NWV, U) hipLaunchKernelGGL((gemv_rows_kernel<T, NB, RMS, R, NWV, U>), grid, blk, 0, st, w, rows, cols, G, rpw, v, out)
+#define LS_GEMV_U(NB, NWV, U) LS_GEMV_R(NB, 1, NWV, U)
     // B <= 3: a row longer than 4 loads per lane is read in one round of 8; B >= 4: a round takes
     // what the row has, up to the 32 input chunks that can be in flight
 #define LS_GEMV(NB, NWV) do { if (per_lane > 4) LS_GEMV_U(NB, NWV, 8); else LS_GEMV_U(NB, NWV, 4); } while (0)
 #define LS_GEMV_B(NB)                                                                  \
     do {                                                                               \
         constexpr int most = 32 / (NB * (Wt<T>::V / 4));                               \
-        if (per_lane <= 1 || most == 1) LS_GEMV_U(NB, 8, 1);                           \
+        if (four) LS_GEMV_R(NB, 4, 8, 4);                                              \
+        else if (per_lane <= 1 || most == 1) LS_GEMV_U(NB, 8, 1);                      \
         else if (per_lane <= 2 || most == 2) LS_GEMV_U(NB, 8, 2);                      \
         else if (per_lane <= 3 || most == 3) LS_GEMV_U(NB, 8, 3);                      \
         else LS_GEMV_U(NB, 8, 4);                                                      \
@@ -520,6 +525,7 @@ static hipError_t gemv_t(const void* W, int rows, int cols, int G, int rpw, cons
         default: return hipErrorInvalidValue;
     }
 #undef LS_GEMV_B
+#undef LS_GEMV_R
 #undef LS_GEMV
 #undef LS_GEMV_U
     return hipGetLastError();
