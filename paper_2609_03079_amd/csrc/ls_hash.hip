@@ -52,7 +52,9 @@ __global__ __launch_bounds__(kThreads) void hash_predict_kernel(int d, int nblk,
     const float* xt = x + (size_t)blockIdx.x * d;
     float acc0 = 0.f, acc1 = 0.f;
     constexpr int kSteps = 8;  // loads in flight together (16 were no faster)
-    for (int j0 = p; j0 < d; j0 += kPart * kSteps) {
+    // (every thread takes the first round, also past a row shorter than kPart: the copy is its part too)
+    for (int base = 0; base < d; base += kPart * kSteps) {
+        const int j0 = base + p;
         float xv[kSteps];
         float2 wv[kSteps];
 #pragma unroll
@@ -61,7 +63,7 @@ __global__ __launch_bounds__(kThreads) void hash_predict_kernel(int d, int nblk,
             xv[i] = xt[j];
             wv[i] = *reinterpret_cast<const float2*>(w1 + (size_t)j * kTau + b0);
         }
-        if (j0 == p) {
+        if (base == 0) {
             // 16-byte copies: tables 2048, hyperplanes 64
             const uint4* src = reinterpret_cast<const uint4*>(tables);
             uint4* dst = reinterpret_cast<uint4*>(tab);

@@ -29,6 +29,9 @@ CASES = {
     "d1024_nb32": lsgen.CONFIGS["llama2_7b_ffn"].with_(n_layers=2, d_model=1024, d_ff=4096, block=128, rank=256),
     "d4096_nb172": lsgen.CONFIGS["llama2_7b_ffn"].with_(n_layers=2),
     "d512_nb300": lsgen.CONFIGS["c1_reglu_512"].with_(n_layers=1, d_ff=9600, block=32),
+    # rows shorter than the 256 partial sums of a hash bit, and one that is no multiple of them
+    **{f"d{d}_nb24": lsgen.CONFIGS["c1_reglu_512"].with_(n_layers=2, d_model=d, d_ff=768, block=32)
+       for d in (64, 128, 192, 320)},
 }
 
 
