@@ -649,7 +649,8 @@ __global__ __launch_bounds__(64 * kWavesDn) void down_mfma_kernel(
         float mx = 0.f;
 #pragma unroll
         for (int i = 0; i < 8; i += 2) mx = fmaxf(fmaxf(mx, fabsf(v[i])), fabsf(v[i + 1]));
-        if (__any(T == LS_F16 ? mx >= limit : mx == INFINITY)) {  // rare
+        const bool inf_met = T != LS_F16 && __any(mx == INFINITY);
+        if (T == LS_F16 ? __any(mx >= limit) : inf_met) {  // rare
             mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
             if (T == LS_F16) {
@@ -690,7 +691,13 @@ __global__ __launch_bounds__(64 * kWavesDn) void down_mfma_kernel(
                 auto pack = [](float lo, float hi) { return (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xffff0000u); };
                 const uint32_t w0 = pack(a0, a1), w1 = pack(b0, b1), w2 = pack(d0, d1);
                 words[0][q] = prt == 0 ? w0 : (prt == 1 ? w1 : w2);
-                if (NF > 1) words[NF - 1][q] = w2;  // (its second half is never used)
+                if constexpr (NF > 1) {
+                    // (its second half is never used); its first half is lanes that keep an infinity
+                    // for the first fragment: it has no third part
+                    words[1][q] = w2;
+                    if (inf_met)
+                        words[1][q] &= (fabsf(a0) < INFINITY ? 0xffffu : 0u) | (fabsf(a1) < INFINITY ? 0xffff0000u : 0u);
+                }
             }
 #pragma unroll
             for (int f = 0; f < NF; ++f) pt[f] = S::from_raw(words[f]);

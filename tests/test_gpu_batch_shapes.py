@@ -122,6 +122,40 @@ def test_batched_inputs_beyond_float16():
 
 
 @pytest.mark.parametrize("dtype", [lsgen.DT_F16, lsgen.DT_BF16])
+@pytest.mark.parametrize("B", [4, 5, 8])
+@pytest.mark.parametrize("block", [40, 64])
+def test_batched_infinite_activation(block, B, dtype):
+    """A product g u beyond fp32 makes one neuron's activation infinite for the tokens that keep it:
+    their outputs are infinite with the sign of the down weight, as on the vector path, and the
+    other tokens' stay finite."""
+    cfg = lsgen.CONFIGS["llama2_7b_ffn"].with_(n_layers=1, d_model=1024, d_ff=6 * block, block=block, rank=64,
+                                               dtype=dtype, prenorm=False, gate_bias=None)
+    w = lsgen.layer_weights(cfg, 0)
+    big = 2 * block + 5
+    w.up[big] = w.gate[big] = lsgen.to_storage(lsgen.decode_bits(w.gate[big], dtype) * np.float32(1024), dtype)
+    f, _ = make_ffn(cfg, max_batch=B, weights=[w])
+    # every token has projection +4 or -4 on the big neuron's row direction, so that its g = u = +-5e20 is
+    # no small difference of large terms: 3e41, or dropped by the gate; the others' g, u are about 1e17
+    r = lsgen.decode_bits(w.gate[big], dtype)
+    r /= np.linalg.norm(r)
+    keeps = np.arange(B) % 2 == 0
+    xs = lsgen.tokens(cfg, 3, 1, B)[0].astype(np.float64)
+    xs += (np.where(keeps, 4.0, -4.0) - xs @ r)[:, None] * r
+    xs = (xs * 2.0 ** 57).astype(np.float32)
+    y = _step(cfg, w, f, xs, list(range(cfg.n_blk)))
+    f.ls_configure(lsffn.LS_CFG_BATCH_MFMA, 0)
+    ref = _step(cfg, w, f, xs, list(range(cfg.n_blk)))
+    assert np.array_equal(np.isinf(ref).all(axis=1), keeps) and not np.isnan(ref).any()
+    for b in range(B):
+        if keeps[b]:
+            assert np.array_equal(y[b], ref[b]), b
+        else:
+            # both accumulate in fp32 (about 1e-6 of y), and so does the sum with x
+            assert y_err(y[b], ref[b]) <= 5e-6, b
+    f.close()
+
+
+@pytest.mark.parametrize("dtype", [lsgen.DT_F16, lsgen.DT_BF16])
 @pytest.mark.parametrize("d,B", [(64, 4), (448, 8), (2880, 5), (4096, 4), (5120, 8), (6144, 6), (4096, 3)])
 def test_decode_step_prepares_the_same_inputs(d, B, dtype):
     """The decode step's selection launch prepares the gate/up kernel's inputs; the separate calls'
