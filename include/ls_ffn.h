@@ -323,9 +323,8 @@ ls_status ls_kernel_timing(ls_ffn* ctx, int32_t kernel, int32_t reset, double* t
  *    (residency then depends on the device being otherwise idle; every wait in
  *    the kernel is bounded, so a workgroup that never starts makes the step fail
  *    with LS_E_DEVICE at ls_ffn_sync instead of hanging).
- *  LS_CFG_BATCH_MFMA: 1 (default) batches of 4 or more tokens, and of 2 or 3
- *    with a long list, run the gate/up and down kernels on the matrix cores when
- *    the weights are 16-bit (activations split into 16-bit parts, fp32
+ *  LS_CFG_BATCH_MFMA: 1 (default) batches of 4 or more tokens run the gate/up
+ *    and down kernels on the matrix cores when the weights are 16-bit (activations split into 16-bit parts, fp32
  *    accumulation; rows longer than the kernels' registers hold need a block that
  *    is a multiple of 32); 0 always uses the vector-ALU kernels.
  *  LS_CFG_TRACE_WG: -1 (default) off; otherwise the fused kernel records

@@ -46,7 +46,7 @@ struct Shape {
     // when that matrix is no larger than the two factors in the weight type.
     int fold;
     // 1: batches of kMfmaMinBatch or more tokens use the matrix-core gate/up and down
-    // kernels when the shape and the list's length allow (16-bit weights).
+    // kernels when the shape allows (16-bit weights).
     int batch_mfma = 1;
     // 1: row-level zero skip in the vector-ALU gate/up and down kernels (up rows only for
     // neurons with a nonzero gate output; down vectors only for groups with a nonzero
@@ -54,7 +54,7 @@ struct Shape {
     int zero_skip = 0;
 };
 
-constexpr int kMfmaMinBatch = 2;
+constexpr int kMfmaMinBatch = 4;
 
 // Fold decision: the product costs 4 n_blk d bytes, the factors (r d + n_blk r) elem bytes.
 inline int predictor_folds(int d, int r, int n_blk, ls_dtype t) {
@@ -93,12 +93,12 @@ struct SplitJob {
     float* meta;     // [2][kSplitSlices][8]: factors the parts were divided by, sums of squares
     float* frag;     // [W][NK][fragments][64] 16-byte operands
     int B, d, NK, W;
-    int bp;          // tokens padded: 2, 4 or 8
+    int bp;          // tokens padded: 4 or 8
     int bf16;
 };
-// Whether the gate/up launch of these arguments (a list of up to n entries) runs that kernel; then
-// the job that prepares it in buf (split_bytes; null: false).
-bool split_job(const Shape& s, int B, int n, const float* x, void* buf, SplitJob* job);
+// Whether the gate/up launch of these arguments runs that kernel; then the job that prepares it in
+// buf (split_bytes; null: false).
+bool split_job(const Shape& s, int B, const float* x, void* buf, SplitJob* job);
 size_t split_bytes(const Shape& s, int max_batch);
 // job: null, or inputs to prepare beside the selection, one more workgroup a slice (the
 // selection has one workgroup, whose time covers theirs)
@@ -108,7 +108,7 @@ hipError_t launch_select(const float* scores, int B, int n_blk, int mode, int k,
 // slot_table: null in resident mode (block b lives at blocks + b*block_bytes); else
 // device int32 [n_blk] giving the cache slot of block b, relative to `blocks`.
 // x: the layer input [B, d]; the RMS scale is applied when s.prenorm
-// job: null, or the prepared inputs (of the same x and list length)
+// job: null, or the prepared inputs (of the same x)
 hipError_t launch_gateup(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                          const float* x, int B, const int32_t* idx, const int32_t* count,
                          int begin, int end, float* a_buf, const SplitJob* job, hipStream_t st);
@@ -156,8 +156,7 @@ struct StageArgs {
 hipError_t launch_stage_consumer(const Shape& s, const StageArgs& p, int grid, bool cooperative, hipStream_t st);
 
 // ---- matrix-core variants for B >= kMfmaMinBatch (ls_mfma.hip) ---------------------------
-bool gateup_on_mfma(const Shape& s, int B, int n);
-bool down_on_mfma(const Shape& s, int B, int n);
+bool mfma_path(const Shape& s, int B);
 hipError_t launch_gateup_mfma(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                               const float* x, int B, const int32_t* idx, const int32_t* count,
                               int begin, int end, float* a_buf, const SplitJob* job, hipStream_t st);

@@ -117,7 +117,7 @@ __device__ __forceinline__ void lds_barrier_m() {
 // against 5.99 for 1 KB of one row per instruction, which would need a transpose through LDS,
 // and 4.3 - 5.1 for 16 rows x 64 bytes, the plain operand layout.
 //
-// The 8 slots of a fragment hold P parts x BP tokens (BP: tokens padded to 2, 4 or 8); with more
+// The 8 slots of a fragment hold P parts x BP tokens (BP: tokens padded to 4 or 8); with more
 // than 8 there are NF fragments.  A part is the 16-bit rounding of what the parts before it left,
 // so P = 2 float16 parts carry 22 bits of an fp32 value and P = 3 bfloat16 parts all 24.  float16
 // parts: the slice is scaled by a power of two to at most 1 in magnitude and the second part by
@@ -879,26 +879,16 @@ static bool resident_ok(const Shape& s, int B) {
 
 // A thresholded gate turns the last bit of a sum into a neuron kept or dropped, and in a stack a
 // neuron into another block of the next layer's list.  Where such a gate was batched on the
-// matrix cores with two-part activations (4 tokens or more, whole K steps a block), the sums
+// matrix cores with two-part activations (whole K steps a block), the sums
 // keep the order and the parts they have always had, so its decisions stay the same.
-static bool keeps_order(const Shape& s, int B) {
-    return s.act == LS_ACT_SWIGLU_THRESH && B >= 4 && s.blk % 32 == 0;
-}
+static bool keeps_order(const Shape& s) { return s.act == LS_ACT_SWIGLU_THRESH && s.blk % 32 == 0; }
 
-// Whether gate/up and down run here for B tokens and a list of up to n entries.  From 4 tokens on
-// always, where a kernel takes the shape; at 2 and 3 once the list's weights are long enough to
-// pay for the kernels' start (about 4 us more than the vector-ALU kernels').  Measured with 2
-// tokens, gate/up: 45 MB 14.6 us on the vector ALU against 15.7 here, 71 MB 21.7 / 20.0, 235 MB
-// 46.3 / 43.2; 3 tokens: 22 MB 11.9 / 12.2, 45 MB 18.1 / 16.6; down, 2 tokens: 45 MB 13.8 / 15.5,
-// 88 MB 25.0 / 20.8; 3 tokens: 22 MB 10.6 / 12.1, 45 MB 18.4 / 15.5.
-static bool mfma_shape(const Shape& s, int B) {
-    return B >= kMfmaMinBatch && s.dtype != LS_F32 && (resident_ok(s, B) || (B >= 4 && s.blk % 32 == 0));
-}
-bool gateup_on_mfma(const Shape& s, int B, int n) {
-    return mfma_shape(s, B) && (B >= 4 || 4.0 * n * s.blk * s.d >= (B == 2 ? 64e6 : 30e6));
-}
-bool down_on_mfma(const Shape& s, int B, int n) {
-    return mfma_shape(s, B) && (B >= 4 || 2.0 * n * s.blk * s.d >= (B == 2 ? 60e6 : 32e6));
+// Whether gate/up and down run here for B tokens.  Two and three stay on the vector ALU: there the
+// kernels' start (about 4 us more) pays only for long lists (7B shape in float16, 2 tokens: 86 blocks
+// 35.5 us on the vector ALU, 31.2 here; 10 blocks 11.9 and 15.1), and the host knows a list's capacity,
+// not its length.
+bool mfma_path(const Shape& s, int B) {
+    return B >= kMfmaMinBatch && s.dtype != LS_F32 && (resident_ok(s, B) || s.blk % 32 == 0);
 }
 
 // Steps of the shortest slice that eight waves or fewer cover a row with (0: none does).
@@ -948,13 +938,12 @@ template <ls_dtype T>
 static hipError_t gateup_resident_t(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* x, int B,
                                     const int32_t* idx, const int32_t* count, int begin, int end, float* a_buf,
                                     const SplitJob* job, hipStream_t st) {
-    if (B <= 2) return gateup_resident_bp<T, 2>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st);
     if (B <= 4) return gateup_resident_bp<T, 4>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st);
     return gateup_resident_bp<T, 8>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st);
 }
 
-bool split_job(const Shape& s, int B, int n, const float* x, void* buf, SplitJob* job) {
-    if (!buf || !s.batch_mfma || s.zero_skip || !gateup_on_mfma(s, B, n) || keeps_order(s, B) || !resident_ok(s, B))
+bool split_job(const Shape& s, int B, const float* x, void* buf, SplitJob* job) {
+    if (!buf || !s.batch_mfma || s.zero_skip || !mfma_path(s, B) || keeps_order(s) || !resident_ok(s, B))
         return false;
     const int NK = slice_steps(s.d), W = (s.d / 64 + NK - 1) / NK;
     job->x = x;
@@ -964,7 +953,7 @@ bool split_job(const Shape& s, int B, int n, const float* x, void* buf, SplitJob
     job->d = s.d;
     job->NK = NK;
     job->W = W;
-    job->bp = B <= 2 ? 2 : (B <= 4 ? 4 : 8);
+    job->bp = B <= 4 ? 4 : 8;
     job->bf16 = s.dtype == LS_BF16;
     return true;
 }
@@ -981,7 +970,7 @@ hipError_t launch_gateup_mfma(const Shape& s, const LayerDev& L, const int32_t* 
                               const float* x, int B, const int32_t* idx, const int32_t* count,
                               int begin, int end, float* a_buf, const SplitJob* job, hipStream_t st) {
     if (end <= begin) return hipSuccess;
-    if (!keeps_order(s, B) && resident_ok(s, B)) {
+    if (!keeps_order(s) && resident_ok(s, B)) {
         return s.dtype == LS_F16 ? gateup_resident_t<LS_F16>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st)
                                  : gateup_resident_t<LS_BF16>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st);
     }
@@ -1082,9 +1071,9 @@ hipError_t launch_down_mfma(const Shape& s, const LayerDev& L, const int32_t* sl
                             uint32_t* cnt, hipStream_t st) {
     const bool one = down_one_tile(s, B, end - begin);
     const int splits = part && !one ? down_splits(s) : 1;
-    if (keeps_order(s, B) && s.dtype == LS_F16)
+    if (keeps_order(s) && s.dtype == LS_F16)
         down_ordered_t<LS_F16>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, part, cnt, st);
-    else if (keeps_order(s, B) && s.dtype == LS_BF16)
+    else if (keeps_order(s) && s.dtype == LS_BF16)
         down_ordered_t<LS_BF16>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, part, cnt, st);
     else if (s.dtype == LS_F16)
         down_mfma_bp<LS_F16, 8>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, cnt, one, st);

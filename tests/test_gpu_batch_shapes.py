@@ -54,9 +54,6 @@ def test_batched_step_at_the_edges(d, block, n_blk, dtype):
 
 @pytest.mark.parametrize("dtype", [lsgen.DT_F16, lsgen.DT_BF16])
 @pytest.mark.parametrize("B,d,block,n_blk", [
-    (2, 4096, 64, 130),   # long lists: 2 and 3 tokens on the matrix cores (gate/up and down)
-    (3, 4096, 64, 66),
-    (3, 4096, 64, 64),    # just below the down projection's length: gate/up there, down not
     (5, 1024, 24, 240),   # parts that begin inside a K step
     (6, 2880, 40, 90),
     (8, 4096, 128, 24),
@@ -75,6 +72,20 @@ def test_long_lists_against_the_vector_path(B, d, block, n_blk, dtype):
     for b in range(B):
         # both accumulate in fp32 (about 1e-6 of y); x_out - x adds an ulp of x_out each
         assert y_err(y[b], ref[b]) <= 5e-6 + 1e-6 / np.max(np.abs(ref[b])), b
+    f.close()
+
+
+@pytest.mark.parametrize("name", ["llama2_7b_ffn", "mistral_7b_ffn"])
+@pytest.mark.parametrize("dtype", [lsgen.DT_F16, lsgen.DT_BF16])
+@pytest.mark.parametrize("B,n_blk", [(2, 130), (3, 66), (3, 5)])
+def test_two_and_three_tokens_run_on_the_vector_path(B, n_blk, dtype, name):
+    """2 and 3 tokens run the vector-ALU kernels whatever the list's capacity: the knob changes no bit."""
+    cfg = lsgen.CONFIGS[name].with_(n_layers=1, d_model=4096, d_ff=64 * n_blk, block=64, rank=64, dtype=dtype)
+    f, (w,) = make_ffn(cfg, max_batch=B)
+    xs = lsgen.tokens(cfg, 3, 1, B)[0]
+    y = _step(cfg, w, f, xs, list(range(n_blk)))
+    f.ls_configure(lsffn.LS_CFG_BATCH_MFMA, 0)
+    assert np.array_equal(y, _step(cfg, w, f, xs, list(range(n_blk))))
     f.close()
 
 
@@ -160,7 +171,7 @@ def test_batched_infinite_activation(block, B, dtype):
 def test_decode_step_prepares_the_same_inputs(d, B, dtype):
     """The decode step's selection launch prepares the gate/up kernel's inputs; the separate calls'
     gate/up prepares its own: the same bits, also for infinite, tiny and zero tokens."""
-    # (3 tokens take the matrix cores from 30 MB of gate/up rows on)
+    # (3 tokens run on the vector path: the step equals the separate calls there too)
     cfg = lsgen.CONFIGS["llama2_7b_ffn"].with_(n_layers=2, d_model=d, d_ff=1024 if B != 3 else 8192, block=32, rank=64,
                                                dtype=dtype, prenorm=d != 448)
     f, _ = make_ffn(cfg, max_batch=B)
