@@ -578,8 +578,14 @@ constexpr int kDnTiles = 4;   // down: 16-column tiles per workgroup, at most (d
 // With splits > 1 the list range is cut into `splits` equal parts (workgroup group + n_groups *
 // part); each part's sum goes to part_out[part][token][column] and finish_parts adds the parts
 // in order.
+// Waves a workgroup: 8 where the parts take two fragments of several tiles, whose sums and operands do
+// not fit the 128 registers that 16 waves leave a lane (7B shape in bfloat16 at B = 8, 172 blocks: with
+// 6 registers spilled 23.8 us, 21.2 on 8 waves).
 template <ls_dtype T, int BP, int NT>
-__global__ __launch_bounds__(64 * kWavesDn) void down_mfma_kernel(
+constexpr int kDnWaves = Part<T>::kParts * BP > 16 && NT > 1 ? 8 : kWavesDn;
+
+template <ls_dtype T, int BP, int NT>
+__global__ __launch_bounds__((64 * kDnWaves<T, BP, NT>)) void down_mfma_kernel(
     const uint8_t* __restrict__ blocks, size_t block_bytes, const int32_t* __restrict__ slot_table,
     const float* __restrict__ a_buf, int B, int F, int d, int blk, int n_blk,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ count, int begin, int end,
@@ -593,7 +599,7 @@ __global__ __launch_bounds__(64 * kWavesDn) void down_mfma_kernel(
     const int n_groups = d / (kColTile * NT);
     const int grp = (int)blockIdx.x % n_groups, sp = (int)blockIdx.x / n_groups;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    constexpr int n_waves = kWavesDn;
+    constexpr int n_waves = kDnWaves<T, BP, NT>;
     const int len = max(0, list_end_m(count, end, n_blk) - begin);
     const int e0 = begin + (int)((long)len * sp / splits);
     const int e1 = begin + (int)((long)len * (sp + 1) / splits);
@@ -723,7 +729,7 @@ __global__ __launch_bounds__(64 * kWavesDn) void down_mfma_kernel(
         run_item(tb);
     }
     // lane l: columns 4 (l / 16) + i of tile j, slot l % 16
-    __shared__ __attribute__((aligned(16))) float part[kWavesDn][NT][NF][16][16];
+    __shared__ __attribute__((aligned(16))) float part[n_waves][NT][NF][16][16];
     const float k = T == LS_F16 ? ldexpf(1.f, ex - Part<T>::kShift * prt) : 1.f;
 #pragma unroll
     for (int j = 0; j < NT; ++j)
@@ -739,10 +745,10 @@ __global__ __launch_bounds__(64 * kWavesDn) void down_mfma_kernel(
         float yp[P];
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            float yw[kWavesDn];
+            float yw[n_waves];
 #pragma unroll
-            for (int w = 0; w < kWavesDn; ++w) yw[w] = part[w][j][p / PF][(p % PF) * BP + t][m16];
-            yp[p] = tree_sum<kWavesDn>(yw);
+            for (int w = 0; w < n_waves; ++w) yw[w] = part[w][j][p / PF][(p % PF) * BP + t][m16];
+            yp[p] = tree_sum<n_waves>(yw);
         }
         float y = yp[P - 1];
 #pragma unroll
@@ -1017,7 +1023,7 @@ static void down_mfma_nt(const Shape& s, const LayerDev& L, const int32_t* slot_
     const bool exact = cpe > 1 && (uint64_t)(s.F / 8) * cpe < (1ull << 32);
     const uint32_t magic = exact ? 0xffffffffu / cpe + 1u : 0u;
     hipLaunchKernelGGL((down_mfma_kernel<T, BP, NT>), dim3((unsigned)(s.d / (kColTile * NT) * splits)),
-                       dim3(64 * kWavesDn), 0, st, L.blocks, bb, slot_table, a_buf, B, s.F, s.d, s.blk, s.n_blk, idx,
+                       dim3(64 * kDnWaves<T, BP, NT>), 0, st, L.blocks, bb, slot_table, a_buf, B, s.F, s.d, s.blk, s.n_blk, idx,
                        count, begin, end, x_in, x_acc, splits, part, cnt, magic);
 }
 
