@@ -324,9 +324,12 @@ ls_status ls_kernel_timing(ls_ffn* ctx, int32_t kernel, int32_t reset, double* t
  *    the kernel is bounded, so a workgroup that never starts makes the step fail
  *    with LS_E_DEVICE at ls_ffn_sync instead of hanging).
  *  LS_CFG_BATCH_MFMA: 1 (default) batches of 4 or more tokens run the gate/up
- *    and down kernels on the matrix cores when the weights are 16-bit (activations split into 16-bit parts, fp32
- *    accumulation; rows longer than the kernels' registers hold need a block that
- *    is a multiple of 32); 0 always uses the vector-ALU kernels.
+ *    and down kernels on the matrix cores when the weights are 16-bit (rows longer
+ *    than the kernels' registers hold need a block that is a multiple of 32).
+ *    Inputs and activations enter as sums of 16-bit parts, with fp32 accumulation:
+ *    three parts, all 24 bits; in blocks that are a multiple of 32 two for float16
+ *    weights (22 bits), and for bfloat16 (16 bits) with a thresholded gate and in
+ *    the gate/up kernel of the longer rows.  0 always uses the vector-ALU kernels.
  *  LS_CFG_TRACE_WG: -1 (default) off; otherwise the fused kernel records
  *    per-layer phase timestamps of that workgroup (see ls_debug_phase_trace).
  *  LS_CFG_ZERO_SKIP: 0 (default) off; 1 row-level zero skip within the

@@ -56,6 +56,11 @@ struct Shape {
 
 constexpr int kMfmaMinBatch = 4;
 
+// 16-bit parts that stand for an fp32 input or activation in the matrix-core kernels: three bfloat16
+// parts hold all its bits; two float16 parts 22, three all of them.  Blocks that are no multiple of 32
+// take three: without these kernels they run on the vector ALU, in fp32.
+inline int input_parts(const Shape& s) { return s.dtype == LS_F16 && s.blk % 32 == 0 ? 2 : 3; }
+
 // Fold decision: the product costs 4 n_blk d bytes, the factors (r d + n_blk r) elem bytes.
 inline int predictor_folds(int d, int r, int n_blk, ls_dtype t) {
     return 4.0 * n_blk * d <= (double)elem_size(t) * ((double)r * d + (double)n_blk * r) ? 1 : 0;
@@ -95,6 +100,7 @@ struct SplitJob {
     int B, d, NK, W;
     int bp;          // tokens padded: 4 or 8
     int bf16;
+    int parts;       // 16-bit parts of an input
 };
 // Whether the gate/up launch of these arguments runs that kernel; then the job that prepares it in
 // buf (split_bytes; null: false).

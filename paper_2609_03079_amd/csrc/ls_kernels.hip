@@ -255,11 +255,14 @@ __global__ __launch_bounds__(Q > 8 ? 512 : 1024) void select_kernel(const float*
         if (threadIdx.x >= 64) return;
         const int w = (int)blockIdx.x - 1, lane = threadIdx.x;
         if (job.bf16) {
-            if (job.bp == 4) split_slice<LS_BF16, 4>(job, w, lane);
-            else split_slice<LS_BF16, 8>(job, w, lane);
+            if (job.bp == 4) split_slice<LS_BF16, 3, 4>(job, w, lane);
+            else split_slice<LS_BF16, 3, 8>(job, w, lane);
+        } else if (job.parts == 3) {
+            if (job.bp == 4) split_slice<LS_F16, 3, 4>(job, w, lane);
+            else split_slice<LS_F16, 3, 8>(job, w, lane);
         } else {
-            if (job.bp == 4) split_slice<LS_F16, 4>(job, w, lane);
-            else split_slice<LS_F16, 8>(job, w, lane);
+            if (job.bp == 4) split_slice<LS_F16, 2, 4>(job, w, lane);
+            else split_slice<LS_F16, 2, 8>(job, w, lane);
         }
         return;
     }

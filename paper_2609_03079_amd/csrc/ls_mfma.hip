@@ -119,9 +119,14 @@ __device__ __forceinline__ void lds_barrier_m() {
 //
 // The 8 slots of a fragment hold P parts x BP tokens (BP: tokens padded to 4 or 8); with more
 // than 8 there are NF fragments.  A part is the 16-bit rounding of what the parts before it left,
-// so P = 2 float16 parts carry 22 bits of an fp32 value and P = 3 bfloat16 parts all 24.  float16
-// parts: the slice is scaled by a power of two to at most 1 in magnitude and the second part by
-// 2^11, so that neither overflows nor goes subnormal; both factors are taken out of the sums.
+// so P = 2 float16 parts carry 22 bits of an fp32 value and P = 3 parts of either type all 24
+// (input_parts).  float16 parts: the slice is scaled by a power of two to below 2 in magnitude and
+// each part by 2^11 against the one before, so that none overflows; the factors are taken out of
+// the sums.  The last part of a value far below the slice's largest is subnormal: three parts hold 24
+// bits down to 2^-23 of the largest and multiples of 2^-46 of it below (two: 22 bits down to 2^-14,
+// multiples of 2^-35).  The third part costs 1.3 to 1.7 us a sparse step (2880 x 7720 at B = 5, 96 blocks
+// of 40: 21.1 -> 22.8); its error against 64 bits, activations and output together, is below the
+// vector-ALU kernels' at every width measured, two parts' is above it at 512.
 //
 // Measured against the staged kernel below (which keeps rows longer than the registers hold):
 // Mistral-7B shape at B = 4 (105 blocks, 220 MB) 61.7 -> 41.6 us, 13B shape at B = 8 (138
@@ -132,7 +137,7 @@ constexpr int kGuWaves = kSplitSlices;  // slices, at most
 // FULL: every wave has NK steps (d / 64 = W NK); the addresses of a unit's loads then differ only in
 // their immediate offsets.  PRE: the fragments (and the slices' scales and sums of squares) were
 // prepared by the selection launch (the same bits); the wave then only loads them.
-template <ls_dtype T, int NK, int BP, bool FULL, bool PRE>
+template <ls_dtype T, int P, int NK, int BP, bool FULL, bool PRE>
 __global__ __launch_bounds__(64 * kGuWaves) void gateup_mfma_kernel(
     const uint8_t* __restrict__ blocks, size_t block_bytes, const int32_t* __restrict__ slot_table,
     const void* __restrict__ bias, float thresh, const float* __restrict__ x, int B, int d, int blk,
@@ -141,7 +146,6 @@ __global__ __launch_bounds__(64 * kGuWaves) void gateup_mfma_kernel(
     const float* __restrict__ meta) {
     using S = Split<T>;
     typedef typename S::vec vec;
-    constexpr int P = Part<T>::kParts;
     constexpr int NF = (P * BP + 7) / 8;
     // loads of a unit: one row set's steps, or half of them where two whole ones and the
     // fragments would not fit the 256 registers
@@ -246,7 +250,7 @@ __global__ __launch_bounds__(64 * kGuWaves) void gateup_mfma_kernel(
 #pragma unroll
         for (int s = 0; s < NK; ++s) {
             u32x4 words[NF];
-            split_step<T, BP>(xv[s], ex, lane, s4, words);
+            split_step<T, P, BP>(xv[s], ex, lane, s4, words);
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
                 asm volatile("" : "+v"(words[f]));
@@ -572,8 +576,8 @@ constexpr int kDnTiles = 4;   // down: 16-column tiles per workgroup, at most (d
 // The 16 columns of operand B hold the activations' parts: BP (4 or 8) tokens each, part
 // (l % 16) / BP (+ 16 / BP in a second fragment, for three parts of 8 tokens).  float16 parts are
 // scaled per token by the largest magnitude the wave has met so far (a power of two; the sums
-// are rescaled when it grows), so that they neither overflow nor go subnormal, and the second
-// part by 2^11.  Two items are in flight per wave.
+// are rescaled when it grows), so that they do not overflow, and each part by 2^11 against the one
+// before (the bits they hold: as for the gate/up kernel's slices).  Two items are in flight per wave.
 //
 // With splits > 1 the list range is cut into `splits` equal parts (workgroup group + n_groups *
 // part); each part's sum goes to part_out[part][token][column] and finish_parts adds the parts
@@ -581,11 +585,11 @@ constexpr int kDnTiles = 4;   // down: 16-column tiles per workgroup, at most (d
 // Waves a workgroup: 8 where the parts take two fragments of several tiles, whose sums and operands do
 // not fit the 128 registers that 16 waves leave a lane (7B shape in bfloat16 at B = 8, 172 blocks: with
 // 6 registers spilled 23.8 us, 21.2 on 8 waves).
-template <ls_dtype T, int BP, int NT>
-constexpr int kDnWaves = Part<T>::kParts * BP > 16 && NT > 1 ? 8 : kWavesDn;
+template <int P, int BP, int NT>
+constexpr int kDnWaves = P * BP > 16 && NT > 1 ? 8 : kWavesDn;
 
-template <ls_dtype T, int BP, int NT>
-__global__ __launch_bounds__((64 * kDnWaves<T, BP, NT>)) void down_mfma_kernel(
+template <ls_dtype T, int P, int BP, int NT>
+__global__ __launch_bounds__((64 * kDnWaves<P, BP, NT>)) void down_mfma_kernel(
     const uint8_t* __restrict__ blocks, size_t block_bytes, const int32_t* __restrict__ slot_table,
     const float* __restrict__ a_buf, int B, int F, int d, int blk, int n_blk,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ count, int begin, int end,
@@ -593,13 +597,12 @@ __global__ __launch_bounds__((64 * kDnWaves<T, BP, NT>)) void down_mfma_kernel(
     float* __restrict__ part_out, uint32_t* __restrict__ cnt, uint32_t cpe_magic) {
     using S = Split<T>;
     typedef typename S::vec vec;
-    constexpr int P = Part<T>::kParts;
     constexpr int PF = 16 / BP;              // parts of one fragment
     constexpr int NF = (P + PF - 1) / PF;
     const int n_groups = d / (kColTile * NT);
     const int grp = (int)blockIdx.x % n_groups, sp = (int)blockIdx.x / n_groups;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    constexpr int n_waves = kDnWaves<T, BP, NT>;
+    constexpr int n_waves = kDnWaves<P, BP, NT>;
     const int len = max(0, list_end_m(count, end, n_blk) - begin);
     const int e0 = begin + (int)((long)len * sp / splits);
     const int e1 = begin + (int)((long)len * (sp + 1) / splits);
@@ -655,8 +658,9 @@ __global__ __launch_bounds__((64 * kDnWaves<T, BP, NT>)) void down_mfma_kernel(
         float mx = 0.f;
 #pragma unroll
         for (int i = 0; i < 8; i += 2) mx = fmaxf(fmaxf(mx, fabsf(v[i])), fabsf(v[i + 1]));
-        const bool inf_met = T != LS_F16 && __any(mx == INFINITY);
-        if (T == LS_F16 ? __any(mx >= limit) : inf_met) {  // rare
+        bool inf_met = false;
+        if (__any(T == LS_F16 ? mx >= limit : mx == INFINITY)) {  // rare
+            inf_met = __any(mx == INFINITY);
             mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
             if (T == LS_F16) {
@@ -664,7 +668,9 @@ __global__ __launch_bounds__((64 * kDnWaves<T, BP, NT>)) void down_mfma_kernel(
 #pragma unroll
                 for (int j = 0; j < NT; ++j)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) c[j][0][i] = ldexpf(c[j][0][i], ex - eg);
+                    for (int f = 0; f < NF; ++f)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) c[j][f][i] = ldexpf(c[j][f][i], ex - eg);
                 ex = eg;
                 s1 = ldexpf(1.f, -ex);
                 limit = ldexpf(1.f, ex + 1);
@@ -674,19 +680,42 @@ __global__ __launch_bounds__((64 * kDnWaves<T, BP, NT>)) void down_mfma_kernel(
                 for (int i = 0; i < 8; ++i) v[i] = fabsf(v[i]) < INFINITY ? v[i] : 0.f;
             }
         }
+        // a second fragment holds third parts (its second half is never used) in lanes that keep an
+        // infinity for the first: it has none
+        auto third_part = [&](u32x4 (&words)[NF]) {
+            if constexpr (NF > 1) {
+                if (inf_met)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        words[1][q] &= (fabsf(v[2 * q]) < INFINITY ? 0xffffu : 0u) |
+                                       (fabsf(v[2 * q + 1]) < INFINITY ? 0xffff0000u : 0u);
+            }
+        };
         vec pt[NF];
         if constexpr (T == LS_F16) {
             typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-            u32x4 words;
+            u32x4 words[NF];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const float a0 = v[2 * q], a1 = v[2 * q + 1];
                 const f16x2 h = {(_Float16)(a0 * s1), (_Float16)(a1 * s1)};
                 const float s2 = s1 * 2048.f;
-                const f16x2 m = {(_Float16)fmaf((float)h.x, -2048.f, a0 * s2), (_Float16)fmaf((float)h.y, -2048.f, a1 * s2)};
-                words[q] = prt ? __builtin_bit_cast(uint32_t, m) : __builtin_bit_cast(uint32_t, h);
+                const float r0 = fmaf((float)h.x, -2048.f, a0 * s2), r1 = fmaf((float)h.y, -2048.f, a1 * s2);
+                const f16x2 m = {(_Float16)r0, (_Float16)r1};
+                const uint32_t w0 = __builtin_bit_cast(uint32_t, h), w1 = __builtin_bit_cast(uint32_t, m);
+                if constexpr (P == 2) {
+                    words[0][q] = prt ? w1 : w0;
+                } else {
+                    const f16x2 l = {(_Float16)fmaf((float)m.x, -2048.f, r0 * 2048.f),
+                                     (_Float16)fmaf((float)m.y, -2048.f, r1 * 2048.f)};
+                    const uint32_t w2 = __builtin_bit_cast(uint32_t, l);
+                    words[0][q] = prt == 0 ? w0 : (prt == 1 ? w1 : w2);
+                    if constexpr (NF > 1) words[1][q] = w2;
+                }
             }
-            pt[0] = S::from_raw(words);
+            third_part(words);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) pt[f] = S::from_raw(words[f]);
         } else {
             auto rest = [](float x) { return x - __uint_as_float(__float_as_uint(x) & 0xffff0000u); };
             u32x4 words[NF];
@@ -697,14 +726,9 @@ __global__ __launch_bounds__((64 * kDnWaves<T, BP, NT>)) void down_mfma_kernel(
                 auto pack = [](float lo, float hi) { return (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xffff0000u); };
                 const uint32_t w0 = pack(a0, a1), w1 = pack(b0, b1), w2 = pack(d0, d1);
                 words[0][q] = prt == 0 ? w0 : (prt == 1 ? w1 : w2);
-                if constexpr (NF > 1) {
-                    // (its second half is never used); its first half is lanes that keep an infinity
-                    // for the first fragment: it has no third part
-                    words[1][q] = w2;
-                    if (inf_met)
-                        words[1][q] &= (fabsf(a0) < INFINITY ? 0xffffu : 0u) | (fabsf(a1) < INFINITY ? 0xffff0000u : 0u);
-                }
+                if constexpr (NF > 1) words[1][q] = w2;
             }
+            third_part(words);
 #pragma unroll
             for (int f = 0; f < NF; ++f) pt[f] = S::from_raw(words[f]);
         }
@@ -730,13 +754,12 @@ __global__ __launch_bounds__((64 * kDnWaves<T, BP, NT>)) void down_mfma_kernel(
     }
     // lane l: columns 4 (l / 16) + i of tile j, slot l % 16
     __shared__ __attribute__((aligned(16))) float part[n_waves][NT][NF][16][16];
-    const float k = T == LS_F16 ? ldexpf(1.f, ex - Part<T>::kShift * prt) : 1.f;
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             f32x4v v = c[j][f];
-            if (T == LS_F16) v *= k;
+            if (T == LS_F16) v *= ldexpf(1.f, ex - Part<T>::kShift * (f * PF + prt));
             *reinterpret_cast<f32x4v*>(&part[wave][j][f][col][4 * (lane >> 4)]) = v;
         }
     __syncthreads();
@@ -877,9 +900,9 @@ __global__ __launch_bounds__(64 * kWavesDn) void down_ordered_kernel(
 }  // namespace
 
 // The resident kernel's registers hold up to 16 steps of 64 values a wave beside the loads in
-// flight, but only 12 where the parts take three fragments (bfloat16, 5 to 8 tokens).
+// flight, but only 12 where the parts take three fragments (three parts, 5 to 8 tokens).
 static bool resident_ok(const Shape& s, int B) {
-    const int nk = s.dtype == LS_BF16 && B > 4 ? 12 : 16;
+    const int nk = input_parts(s) == 3 && B > 4 ? 12 : 16;
     return s.d <= 64 * nk * kGuWaves;
 }
 
@@ -904,7 +927,7 @@ static int slice_steps(int d) {
     return 0;
 }
 
-template <ls_dtype T, int BP>
+template <ls_dtype T, int P, int BP>
 static hipError_t gateup_resident_bp(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* x, int B,
                                      const int32_t* idx, const int32_t* count, int begin, int end, float* a_buf,
                                      const SplitJob* job, hipStream_t st) {
@@ -913,7 +936,7 @@ static hipError_t gateup_resident_bp(const Shape& s, const LayerDev& L, const in
     const long groups = (long)(end - begin) * (s.blk / 8);
     const int cus = std::max(1, cu_count());
 #define LS_GUR_K(NK, FULL, PRE)                                                                                        \
-    hipLaunchKernelGGL((gateup_mfma_kernel<T, NK, BP, FULL, PRE>), dim3((unsigned)grid), dim3(64 * W), 0, st, L.blocks,  \
+    hipLaunchKernelGGL((gateup_mfma_kernel<T, P, NK, BP, FULL, PRE>), dim3((unsigned)grid), dim3(64 * W), 0, st, L.blocks,  \
                        bb, slot_table, L.bias, L.threshold, x, B, s.d, s.blk, s.n_blk, s.F, idx, count, begin, end,    \
                        a_buf, s.act == LS_ACT_REGLU ? 1 : 0, s.prenorm, reinterpret_cast<const u32x4*>(job ? job->frag : nullptr),      \
                        job ? job->meta : nullptr)
@@ -931,7 +954,7 @@ static hipError_t gateup_resident_bp(const Shape& s, const LayerDev& L, const in
         case 10: LS_GUR(10); break;
         case 12: LS_GUR(12); break;
         case 16:
-            if constexpr (T == LS_F16 || BP <= 4) { LS_GUR(16); break; }
+            if constexpr (P == 2 || BP <= 4) { LS_GUR(16); break; }
             return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
@@ -940,12 +963,12 @@ static hipError_t gateup_resident_bp(const Shape& s, const LayerDev& L, const in
     return hipGetLastError();
 }
 
-template <ls_dtype T>
+template <ls_dtype T, int P>
 static hipError_t gateup_resident_t(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* x, int B,
                                     const int32_t* idx, const int32_t* count, int begin, int end, float* a_buf,
                                     const SplitJob* job, hipStream_t st) {
-    if (B <= 4) return gateup_resident_bp<T, 4>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st);
-    return gateup_resident_bp<T, 8>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st);
+    if (B <= 4) return gateup_resident_bp<T, P, 4>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st);
+    return gateup_resident_bp<T, P, 8>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st);
 }
 
 bool split_job(const Shape& s, int B, const float* x, void* buf, SplitJob* job) {
@@ -961,6 +984,7 @@ bool split_job(const Shape& s, int B, const float* x, void* buf, SplitJob* job) 
     job->W = W;
     job->bp = B <= 4 ? 4 : 8;
     job->bf16 = s.dtype == LS_BF16;
+    job->parts = input_parts(s);
     return true;
 }
 
@@ -977,8 +1001,10 @@ hipError_t launch_gateup_mfma(const Shape& s, const LayerDev& L, const int32_t* 
                               int begin, int end, float* a_buf, const SplitJob* job, hipStream_t st) {
     if (end <= begin) return hipSuccess;
     if (!keeps_order(s) && resident_ok(s, B)) {
-        return s.dtype == LS_F16 ? gateup_resident_t<LS_F16>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st)
-                                 : gateup_resident_t<LS_BF16>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st);
+        auto launch = s.dtype == LS_BF16 ? gateup_resident_t<LS_BF16, 3>
+                    : input_parts(s) == 3 ? gateup_resident_t<LS_F16, 3>
+                                          : gateup_resident_t<LS_F16, 2>;
+        return launch(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st);
     }
     const long groups = (long)(end - begin) * (s.blk / 16);
     const size_t bb = s.block_elems * elem_size(s.dtype);
@@ -1014,7 +1040,7 @@ static int down_splits(const Shape& s) {
     return std::min(kDownPartsMax, std::max(1, cu_count() / (s.d / (kColTile * kDnTiles))));
 }
 
-template <ls_dtype T, int BP, int NT>
+template <ls_dtype T, int P, int BP, int NT>
 static void down_mfma_nt(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* a_buf, int B,
                          const int32_t* idx, const int32_t* count, int begin, int end, const float* x_in, float* x_acc,
                          int splits, float* part, uint32_t* cnt, hipStream_t st) {
@@ -1022,8 +1048,8 @@ static void down_mfma_nt(const Shape& s, const LayerDev& L, const int32_t* slot_
     const uint32_t cpe = (uint32_t)s.blk / 8u;
     const bool exact = cpe > 1 && (uint64_t)(s.F / 8) * cpe < (1ull << 32);
     const uint32_t magic = exact ? 0xffffffffu / cpe + 1u : 0u;
-    hipLaunchKernelGGL((down_mfma_kernel<T, BP, NT>), dim3((unsigned)(s.d / (kColTile * NT) * splits)),
-                       dim3(64 * kDnWaves<T, BP, NT>), 0, st, L.blocks, bb, slot_table, a_buf, B, s.F, s.d, s.blk, s.n_blk, idx,
+    hipLaunchKernelGGL((down_mfma_kernel<T, P, BP, NT>), dim3((unsigned)(s.d / (kColTile * NT) * splits)),
+                       dim3(64 * kDnWaves<P, BP, NT>), 0, st, L.blocks, bb, slot_table, a_buf, B, s.F, s.d, s.blk, s.n_blk, idx,
                        count, begin, end, x_in, x_acc, splits, part, cnt, magic);
 }
 
@@ -1037,14 +1063,14 @@ static bool down_one_tile(const Shape& s, int B, int n) {
     return s.d / kColTile <= cu_count() && 2.0 * B * n * s.blk * s.d <= 80e6;
 }
 
-template <ls_dtype T, int BP>
+template <ls_dtype T, int P, int BP>
 static void down_mfma_bp(const Shape& s, const LayerDev& L, const int32_t* slot_table, const float* a_buf, int B,
                          const int32_t* idx, const int32_t* count, int begin, int end, const float* x_in, float* x_acc,
                          int splits, float* part, uint32_t* cnt, bool one, hipStream_t st) {
     if (one)
-        down_mfma_nt<T, BP, 1>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, 1, part, cnt, st);
+        down_mfma_nt<T, P, BP, 1>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, 1, part, cnt, st);
     else
-        down_mfma_nt<T, BP, kDnTiles>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, cnt, st);
+        down_mfma_nt<T, P, BP, kDnTiles>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, cnt, st);
 }
 
 // The order of a thresholded gate's down projection: list parts and waves by shape (tiles that
@@ -1081,13 +1107,12 @@ hipError_t launch_down_mfma(const Shape& s, const LayerDev& L, const int32_t* sl
         down_ordered_t<LS_F16>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, part, cnt, st);
     else if (keeps_order(s) && s.dtype == LS_BF16)
         down_ordered_t<LS_BF16>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, part, cnt, st);
-    else if (s.dtype == LS_F16)
-        down_mfma_bp<LS_F16, 8>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, cnt, one, st);
-    else if (s.dtype == LS_BF16 && B <= 4)
-        down_mfma_bp<LS_BF16, 4>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, cnt, one, st);
-    else if (s.dtype == LS_BF16)
-        down_mfma_bp<LS_BF16, 8>(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, cnt, one, st);
-    else
+    else if (s.dtype == LS_F16 || s.dtype == LS_BF16) {
+        auto launch = s.dtype == LS_BF16      ? (B <= 4 ? down_mfma_bp<LS_BF16, 3, 4> : down_mfma_bp<LS_BF16, 3, 8>)
+                      : input_parts(s) == 3 ? (B <= 4 ? down_mfma_bp<LS_F16, 3, 4> : down_mfma_bp<LS_F16, 3, 8>)
+                                            : down_mfma_bp<LS_F16, 2, 8>;
+        launch(s, L, slot_table, a_buf, B, idx, count, begin, end, x_in, x_acc, splits, part, cnt, one, st);
+    } else
         return hipErrorInvalidValue;
     return hipGetLastError();
 }

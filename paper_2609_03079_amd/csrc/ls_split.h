@@ -21,13 +21,13 @@ __device__ __forceinline__ float tree_sum(const float (&v)[N]) {
 }
 
 // Parts of values, two at a time (a word holds the pair's 16-bit parts).  pack() takes the
-// leading parts, rest() the (scaled) remainder; a value that is not finite leaves none.
+// leading parts, rest() the (scaled) remainder; a value that is not finite leaves none.  How many
+// parts P: input_parts (ls_internal.h).
 template <ls_dtype T>
 struct Part;
 template <>
 struct Part<LS_F16> {
-    static constexpr int kParts = 2;
-    static constexpr int kShift = 11;  // the second part is scaled by 2^11
+    static constexpr int kShift = 11;  // each part is scaled by 2^11 against the one before
     typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     __device__ static inline uint32_t pack(float a, float b) {
         const f16x2 h = {(_Float16)a, (_Float16)b};
@@ -40,8 +40,7 @@ struct Part<LS_F16> {
 };
 template <>
 struct Part<LS_BF16> {
-    static constexpr int kParts = 3;   // 8 bits each, cut off: exact
-    static constexpr int kShift = 0;
+    static constexpr int kShift = 0;   // (8 bits each, cut off: three are exact)
     // the upper halves of two values (a NaN stays one: its quiet bit is set)
     __device__ static inline uint32_t pack(float a, float b) {
         const uint32_t ua = __float_as_uint(a) | (a != a ? 0x400000u : 0u);
@@ -57,10 +56,9 @@ struct Part<LS_BF16> {
 // One step of 64 values: this lane's 8 values x (chunk 2 (lane / 16) + (lane / 8) % 2 of its token) as
 // the words of its operand in each fragment, scaled by 2^-ex first (float16); the values' squares
 // go into the four chains s4.
-template <ls_dtype T, int BP>
+template <ls_dtype T, int P, int BP>
 __device__ __forceinline__ void split_step(const f32x4 (&x)[2], int ex, int lane, float (&s4)[4],
-                                           u32x4 (&words)[(Part<T>::kParts * BP + 7) / 8]) {
-    constexpr int P = Part<T>::kParts;
+                                           u32x4 (&words)[(P * BP + 7) / 8]) {
     constexpr int NF = (P * BP + 7) / 8;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -97,9 +95,9 @@ __device__ __forceinline__ int split_exponent(float mx) {
 
 // One wave: slice `w` of a job, written where the resident kernel's wave w reads it.  The loads of
 // four steps are in flight together.
-template <ls_dtype T, int BP>
+template <ls_dtype T, int P, int BP>
 __device__ __forceinline__ void split_slice(const SplitJob& p, int w, int lane) {
-    constexpr int NF = (Part<T>::kParts * BP + 7) / 8;
+    constexpr int NF = (P * BP + 7) / 8;
     const int steps = p.d / 64;
     const int s0 = steps * w / p.W, nst = steps * (w + 1) / p.W - s0;
     const int tok = (lane & 7) & (BP - 1);
@@ -141,7 +139,7 @@ __device__ __forceinline__ void split_slice(const SplitJob& p, int w, int lane) 
             if (s + u >= p.NK) break;
             u32x4 words[NF];
             if (s + u < nst) {
-                split_step<T, BP>(xv[u], ex, lane, s4, words);
+                split_step<T, P, BP>(xv[u], ex, lane, s4, words);
             } else {
 #pragma unroll
                 for (int f = 0; f < NF; ++f) words[f] = u32x4{0u, 0u, 0u, 0u};

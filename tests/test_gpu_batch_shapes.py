@@ -132,6 +132,77 @@ def test_batched_inputs_beyond_float16():
     f.close()
 
 
+def _acts_and_out(cfg, f, xs, ids):
+    """Activations (list order) and outputs of one sparse step, in 64 bits."""
+    B = len(xs)
+    out, acts = empty_f32(B, cfg.d_model), empty_f32(B, cfg.d_ff)
+    idx = torch.tensor(ids, dtype=torch.int32, device="cuda")
+    cnt = torch.tensor([len(ids)], dtype=torch.int32, device="cuda")
+    f.ls_sparse_ffn_step(0, dev_f32(xs), B, idx, cnt, 0, len(ids), out)
+    f.ls_debug_last_activations(acts)
+    return host(acts).astype(np.float64), host(out).astype(np.float64)
+
+
+# float16: the matrix unit aligns a step's products to its largest exponent, and a zero weight counts as 2^-14 there:
+# 24 bits below 2^-14 of the large value, 2^-16 of a value 2^-22 of it (measured: 7e-6 of a row's sum).  Whole K steps
+# have two parts, multiples of 2^-35 of the scale, which is at least half the largest: 2^-13 of such a value
+# (measured: 5e-5 of a sum of hundreds)
+@pytest.mark.parametrize("dtype,block,tol", [(lsgen.DT_F16, 24, 2e-5), (lsgen.DT_F16, 40, 2e-5), (lsgen.DT_F16, 64, 2e-4),
+                                             (lsgen.DT_BF16, 40, 2e-6), (lsgen.DT_BF16, 64, 2e-6)])
+@pytest.mark.parametrize("B", [4, 5, 8])
+def test_batched_small_values_beside_large_ones(B, dtype, block, tol):
+    """Inputs 2^-22 of a slice's largest, and activations 2^-22 of a token's largest, where the large
+    one's weight is zero: the small ones' sums keep the precision of their parts."""
+    n_blk = 64
+    cfg = lsgen.CONFIGS["llama2_7b_ffn"].with_(n_layers=1, d_model=2048, d_ff=n_blk * block, block=block, rank=64,
+                                               dtype=dtype, prenorm=False, gate_bias=None)
+    w = lsgen.layer_weights(cfg, 0)
+    small = np.float32(2.0 ** -22)
+
+    def put(m, rows, cols, values):
+        x = lsgen.decode_bits(m, dtype).astype(np.float32).reshape(m.shape)
+        x[rows, cols] = values
+        return lsgen.to_storage(x, dtype).reshape(m.shape)
+
+    every = slice(None)
+    # one input of 1 in every 64 that no row looks at, beside inputs of 2^-22
+    w.gate, w.up = (put(m, every, slice(0, None, 64), 0.0) for m in (w.gate, w.up))
+    f, _ = make_ffn(cfg, max_batch=B, weights=[w])
+    xs = lsgen.tokens(cfg, 3, 1, B)[0]
+    xs *= small
+    xs[:, ::64] = 1.0
+    ids = list(range(n_blk))[::-1]
+    a, _ = _acts_and_out(cfg, f, xs, ids)
+    f.close()
+    gate, up = (lsgen.decode_bits(m, dtype).reshape(m.shape) for m in (w.gate, w.up))
+    order = np.concatenate([np.arange(b * block, (b + 1) * block) for b in ids])
+    x64 = xs.astype(np.float64)
+    ref = np.maximum(x64 @ gate[order].T, 0.0) * (x64 @ up[order].T)
+    for b in range(B):
+        assert y_err(a[b], ref[b]) <= tol, ("activations", b)
+
+    # neurons whose down column is zero and whose activations are 2^22 of the others': rows of 2^11 times the
+    # last input alone; one in every 32 of the list's later half, so that a wave's scale grows on the way.
+    # The first half of the inputs is zero: those outputs are the sums alone
+    w = lsgen.layer_weights(cfg, 0)
+    big = order[len(order) // 2:][::32]
+    w.gate, w.up = (put(m, big, every, 0.0) for m in (w.gate, w.up))
+    w.gate, w.up = (put(m, big, -1, 2.0 ** 11) for m in (w.gate, w.up))
+    w.down = put(w.down, every, big, 0.0)
+    f, _ = make_ffn(cfg, max_batch=B, weights=[w])
+    down = lsgen.decode_bits(w.down, dtype).reshape(w.down.shape)
+    xs = lsgen.tokens(cfg, 3, 1, B)[0]
+    half = cfg.d_model // 2
+    xs[:, :half] = 0.0
+    xs[:, -1] = 1.0
+    a, out = _acts_and_out(cfg, f, xs, ids)
+    f.close()
+    assert np.all(np.max(np.abs(a), axis=1) > 2.0 ** 20 * np.median(np.abs(a[a != 0])))
+    ref = a @ down[:half, order].T
+    for b in range(B):
+        assert y_err(out[b, :half], ref[b]) <= tol, ("outputs", b)
+
+
 @pytest.mark.parametrize("dtype", [lsgen.DT_F16, lsgen.DT_BF16])
 @pytest.mark.parametrize("B", [4, 5, 8])
 @pytest.mark.parametrize("block", [40, 64])
