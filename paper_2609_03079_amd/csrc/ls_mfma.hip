@@ -581,7 +581,9 @@ constexpr int kDnTiles = 4;   // down: 16-column tiles per workgroup, at most (d
 //
 // With splits > 1 the list range is cut into `splits` equal parts (workgroup group + n_groups *
 // part); each part's sum goes to part_out[part][token][column] and finish_parts adds the parts
-// in order.
+// in order.  A list of up to one item per wave is not: the host chooses by the list's capacity, and
+// there the sum over parts costs 1 to 2 us (a sparse step of 2880 x 7720 in blocks of 40 at B = 4, 9 of
+// 193 blocks listed: 16.0 -> 14.9 us; 1984 x 5280 in blocks of 24, 11 of 220: 13.9 -> 12.5).
 // Waves a workgroup: 8 where the parts take two fragments of several tiles, whose sums and operands do
 // not fit the 128 registers that 16 waves leave a lane (7B shape in bfloat16 at B = 8, 172 blocks: with
 // 6 registers spilled 23.8 us, 21.2 on 8 waves).
@@ -604,6 +606,10 @@ __global__ __launch_bounds__((64 * kDnWaves<P, BP, NT>)) void down_mfma_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     constexpr int n_waves = kDnWaves<P, BP, NT>;
     const int len = max(0, list_end_m(count, end, n_blk) - begin);
+    if ((long)len * blk <= 32 * n_waves) {  // every item has a wave: not cut
+        if (sp > 0) return;
+        splits = 1;
+    }
     const int e0 = begin + (int)((long)len * sp / splits);
     const int e1 = begin + (int)((long)len * (sp + 1) / splits);
     const size_t piece = (size_t)blk * kColTile * 2;  // bytes of one tile's piece

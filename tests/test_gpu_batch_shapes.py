@@ -23,12 +23,13 @@ SHAPES = [(64, 32, 4), (448, 32, 5), (2048, 64, 4), (2880, 64, 4), (3072, 32, 4)
           (6144, 32, 4), (8192, 32, 4), (8256, 32, 4), (64, 8, 5), (320, 40, 7), (1024, 24, 9), (2048, 128, 4)]
 
 
-def _step(cfg, w, f, xs, ids):
-    B = len(xs)
-    idx = torch.tensor(ids, dtype=torch.int32, device="cuda")
+def _step(cfg, w, f, xs, ids, cap=0):
+    """FFN output of one sparse step over the list ids in a buffer of cap (or just as many) entries."""
+    B, cap = len(xs), max(cap, len(ids))
+    idx = torch.tensor(list(ids) + [0] * (cap - len(ids)), dtype=torch.int32, device="cuda")
     cnt = torch.tensor([len(ids)], dtype=torch.int32, device="cuda")
     out = empty_f32(B, cfg.d_model)
-    f.ls_sparse_ffn_step(0, dev_f32(xs), B, idx, cnt, 0, len(ids), out)
+    f.ls_sparse_ffn_step(0, dev_f32(xs), B, idx, cnt, 0, cap, out)
     return host(out).astype(np.float64) - xs
 
 
@@ -54,7 +55,9 @@ def test_batched_step_at_the_edges(d, block, n_blk, dtype):
 
 @pytest.mark.parametrize("dtype", [lsgen.DT_F16, lsgen.DT_BF16])
 @pytest.mark.parametrize("B,d,block,n_blk", [
-    (5, 1024, 24, 240),   # parts that begin inside a K step
+    (4, 1024, 24, 240),   # parts that begin inside a K step
+    (5, 1024, 24, 240),
+    (4, 320, 40, 220),
     (6, 2880, 40, 90),
     (8, 4096, 128, 24),
 ])
@@ -72,6 +75,31 @@ def test_long_lists_against_the_vector_path(B, d, block, n_blk, dtype):
     for b in range(B):
         # both accumulate in fp32 (about 1e-6 of y); x_out - x adds an ulp of x_out each
         assert y_err(y[b], ref[b]) <= 5e-6 + 1e-6 / np.max(np.abs(ref[b])), b
+    f.close()
+
+
+@pytest.mark.parametrize("dtype", [lsgen.DT_F16, lsgen.DT_BF16])
+@pytest.mark.parametrize("B,block", [(4, 32), (4, 40), (5, 40), (8, 24), (8, 64)])
+def test_short_lists_in_long_buffers(B, block, dtype):
+    """A list of up to one K step per wave is not cut in parts whatever its capacity, a longer one is:
+    empty, one entry, and around 8 and 16 waves, one after the other (each leaves the counts of finished
+    parts at zero for the next)."""
+    cfg = lsgen.CONFIGS["llama2_7b_ffn"].with_(n_layers=1, d_model=2048, d_ff=block * 96, block=block, rank=64,
+                                               dtype=dtype)
+    f, (w,) = make_ffn(cfg, max_batch=B)
+    xs = lsgen.tokens(cfg, 3, 1, B)[0]
+    lists = [list(range(95, 95 - n, -1))
+             for n in (0, 1, 256 // block, 256 // block + 1, 512 // block, 512 // block + 1, 96, 2)]
+    ys = [_step(cfg, w, f, xs, ids, cap=96) for ids in lists]
+    f.ls_configure(lsffn.LS_CFG_BATCH_MFMA, 0)
+    for ids, y in zip(lists, ys):
+        ref = _step(cfg, w, f, xs, ids, cap=96)
+        if not ids:
+            assert not y.any() and not ref.any()
+            continue
+        for b in range(B):
+            # both accumulate in fp32 (about 1e-6 of y); x_out - x adds an ulp of x_out each
+            assert y_err(y[b], ref[b]) <= 5e-6 + 1e-6 / max(np.max(np.abs(ref[b])), 1e-6), (len(ids), b)
     f.close()
 
 
@@ -210,8 +238,9 @@ def test_batched_infinite_activation(block, B, dtype):
     """A product g u beyond fp32 makes one neuron's activation infinite for the tokens that keep it:
     their outputs are infinite with the sign of the down weight, as on the vector path, and the
     other tokens' stay finite."""
-    cfg = lsgen.CONFIGS["llama2_7b_ffn"].with_(n_layers=1, d_model=1024, d_ff=6 * block, block=block, rank=64,
-                                               dtype=dtype, prenorm=False, gate_bias=None)
+    # (64 blocks of 40: past the lists that run on the vector path)
+    cfg = lsgen.CONFIGS["llama2_7b_ffn"].with_(n_layers=1, d_model=1024, d_ff=(64 if block == 40 else 6) * block,
+                                               block=block, rank=64, dtype=dtype, prenorm=False, gate_bias=None)
     w = lsgen.layer_weights(cfg, 0)
     big = 2 * block + 5
     w.up[big] = w.gate[big] = lsgen.to_storage(lsgen.decode_bits(w.gate[big], dtype) * np.float32(1024), dtype)
