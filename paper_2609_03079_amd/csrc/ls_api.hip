@@ -1177,7 +1177,7 @@ ls_status ls_decode_step(ls_ffn* c, float* x, int32_t B, int32_t k) {
         } else {
             // the selection's launch also prepares the inputs of the gate/up kernels that take them so
             ls::SplitJob job{};
-            const ls::SplitJob* pre = ls::split_job(s, B, cur, c->split, &job) ? &job : nullptr;
+            const ls::SplitJob* pre = ls::split_job(s, B, cap, cur, c->split, &job) ? &job : nullptr;
             LS_HIP(c, timed(c, LS_K_SELECT, [&] {
                 return ls::launch_select(c->scores, B, s.n_blk, LS_SEL_TOPK, k, 0.f, 1, cap, c->idx, c->count, pre,
                                          c->stream);

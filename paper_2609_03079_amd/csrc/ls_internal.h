@@ -46,7 +46,7 @@ struct Shape {
     // when that matrix is no larger than the two factors in the weight type.
     int fold;
     // 1: batches of kMfmaMinBatch or more tokens use the matrix-core gate/up and down
-    // kernels when the shape allows (16-bit weights).
+    // kernels when the shape and the list's capacity allow (16-bit weights).
     int batch_mfma = 1;
     // 1: row-level zero skip in the vector-ALU gate/up and down kernels (up rows only for
     // neurons with a nonzero gate output; down vectors only for groups with a nonzero
@@ -102,9 +102,9 @@ struct SplitJob {
     int bf16;
     int parts;       // 16-bit parts of an input
 };
-// Whether the gate/up launch of these arguments runs that kernel; then the job that prepares it in
-// buf (split_bytes; null: false).
-bool split_job(const Shape& s, int B, const float* x, void* buf, SplitJob* job);
+// Whether the gate/up launch of these arguments (a list of up to n entries) runs that kernel; then
+// the job that prepares it in buf (split_bytes; null: false).
+bool split_job(const Shape& s, int B, int n, const float* x, void* buf, SplitJob* job);
 size_t split_bytes(const Shape& s, int max_batch);
 // job: null, or inputs to prepare beside the selection, one more workgroup a slice (the
 // selection has one workgroup, whose time covers theirs)
@@ -114,7 +114,7 @@ hipError_t launch_select(const float* scores, int B, int n_blk, int mode, int k,
 // slot_table: null in resident mode (block b lives at blocks + b*block_bytes); else
 // device int32 [n_blk] giving the cache slot of block b, relative to `blocks`.
 // x: the layer input [B, d]; the RMS scale is applied when s.prenorm
-// job: null, or the prepared inputs (of the same x)
+// job: null, or the prepared inputs (of the same x and list capacity)
 hipError_t launch_gateup(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                          const float* x, int B, const int32_t* idx, const int32_t* count,
                          int begin, int end, float* a_buf, const SplitJob* job, hipStream_t st);
@@ -162,7 +162,7 @@ struct StageArgs {
 hipError_t launch_stage_consumer(const Shape& s, const StageArgs& p, int grid, bool cooperative, hipStream_t st);
 
 // ---- matrix-core variants for B >= kMfmaMinBatch (ls_mfma.hip) ---------------------------
-bool mfma_path(const Shape& s, int B);
+bool mfma_path(const Shape& s, int B, int n);
 hipError_t launch_gateup_mfma(const Shape& s, const LayerDev& L, const int32_t* slot_table,
                               const float* x, int B, const int32_t* idx, const int32_t* count,
                               int begin, int end, float* a_buf, const SplitJob* job, hipStream_t st);

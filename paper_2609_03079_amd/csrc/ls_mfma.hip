@@ -918,12 +918,19 @@ static bool resident_ok(const Shape& s, int B) {
 // keep the order and the parts they have always had, so its decisions stay the same.
 static bool keeps_order(const Shape& s) { return s.act == LS_ACT_SWIGLU_THRESH && s.blk % 32 == 0; }
 
-// Whether gate/up and down run here for B tokens.  Two and three stay on the vector ALU: there the
-// kernels' start (about 4 us more) pays only for long lists (7B shape in float16, 2 tokens: 86 blocks
-// 35.5 us on the vector ALU, 31.2 here; 10 blocks 11.9 and 15.1), and the host knows a list's capacity,
-// not its length.
-bool mfma_path(const Shape& s, int B) {
-    return B >= kMfmaMinBatch && s.dtype != LS_F32 && (resident_ok(s, B) || s.blk % 32 == 0);
+// Whether gate/up and down run here for B tokens and a list of up to n entries.  Two and three stay on
+// the vector ALU: there the kernels' start (about 4 us more) pays only for long lists (7B shape in
+// float16, 2 tokens: 86 blocks 35.5 us on the vector ALU, 31.2 here; 10 blocks 11.9 and 15.1), and the
+// host knows a list's capacity, not its length.  With four and five, blocks that are no multiple of 32
+// stay there where the capacity itself is short: 2880 values a row and blocks of 40 in float16, 4 tokens,
+// 9 blocks 11.7 us on the vector ALU, 14.0 here, 48 blocks 18.4 and 17.8; 5 tokens, 24 blocks 14.5 and
+// 15.2; 1984 and blocks of 24, 5 tokens, 27 blocks 12.1 and 12.5, 55 15.8 and 14.1.  (A threshold's
+// capacity is all blocks: those calls take 1 to 3 us more than there with under a sixth of them
+// listed, 2.5 less with a quarter, 13 with half.)  At 6 tokens and more every length is faster here.
+bool mfma_path(const Shape& s, int B, int n) {
+    if (B < kMfmaMinBatch || s.dtype == LS_F32) return false;
+    if (s.blk % 32 == 0) return true;
+    return resident_ok(s, B) && (B > 5 || (double)n * s.blk * s.d > (B == 4 ? 2.5e6 : 1.5e6));
 }
 
 // Steps of the shortest slice that eight waves or fewer cover a row with (0: none does).
@@ -977,8 +984,8 @@ static hipError_t gateup_resident_t(const Shape& s, const LayerDev& L, const int
     return gateup_resident_bp<T, P, 8>(s, L, slot_table, x, B, idx, count, begin, end, a_buf, job, st);
 }
 
-bool split_job(const Shape& s, int B, const float* x, void* buf, SplitJob* job) {
-    if (!buf || !s.batch_mfma || s.zero_skip || !mfma_path(s, B) || keeps_order(s) || !resident_ok(s, B))
+bool split_job(const Shape& s, int B, int n, const float* x, void* buf, SplitJob* job) {
+    if (!buf || !s.batch_mfma || s.zero_skip || !mfma_path(s, B, n) || keeps_order(s) || !resident_ok(s, B))
         return false;
     const int NK = slice_steps(s.d), W = (s.d / 64 + NK - 1) / NK;
     job->x = x;

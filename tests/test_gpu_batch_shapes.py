@@ -103,6 +103,24 @@ def test_short_lists_in_long_buffers(B, block, dtype):
     f.close()
 
 
+@pytest.mark.parametrize("dtype", [lsgen.DT_F16, lsgen.DT_BF16])
+@pytest.mark.parametrize("B,n", [(4, 30), (4, 31), (5, 18), (5, 19)])
+def test_short_buffers_of_odd_blocks_run_on_the_vector_path(B, n, dtype):
+    """Blocks that are no multiple of 32: up to 2.5e6 values a matrix at 4 tokens, 1.5e6 at 5, the knob
+    changes no bit; one entry more, and sums of another order agree."""
+    cfg = lsgen.CONFIGS["llama2_7b_ffn"].with_(n_layers=1, d_model=2048, d_ff=40 * 40, block=40, rank=64, dtype=dtype)
+    f, (w,) = make_ffn(cfg, max_batch=B)
+    xs = lsgen.tokens(cfg, 3, 1, B)[0]
+    y = _step(cfg, w, f, xs, list(range(n)))
+    f.ls_configure(lsffn.LS_CFG_BATCH_MFMA, 0)
+    ref = _step(cfg, w, f, xs, list(range(n)))
+    short = n * cfg.block * cfg.d_model <= (2.5e6 if B == 4 else 1.5e6)
+    assert short == (n in (30, 18)) and np.array_equal(y, ref) == short
+    for b in range(B):
+        assert y_err(y[b], ref[b]) <= 5e-6 + 1e-6 / np.max(np.abs(ref[b])), b
+    f.close()
+
+
 @pytest.mark.parametrize("name", ["llama2_7b_ffn", "mistral_7b_ffn"])
 @pytest.mark.parametrize("dtype", [lsgen.DT_F16, lsgen.DT_BF16])
 @pytest.mark.parametrize("B,n_blk", [(2, 130), (3, 66), (3, 5)])
