@@ -15,8 +15,8 @@
 // so the codes are reproducible).  The kernel is bound by latency (161 KB through one compute
 // unit), so the 8 hash bits are spread over four groups of 256 threads, two bits each, whose loads
 // of eight steps are in flight together, and only the first two halvings cross waves: 8 tokens at
-// d = 4096 with the selection after it 9.84 -> 9.34 us (launches take most of what is left).  The four binary layers run in one wave (lane b evaluates hash bit b; a
-// ballot forms the bucket).
+// d = 4096 with the selection after it 9.84 -> 9.34 us (this kernel 5.8 of them, the selection 4.0).
+// The four binary layers run in one wave (lane b evaluates hash bit b; a ballot forms the bucket).
 #include "ls_internal.h"
 
 namespace ls {

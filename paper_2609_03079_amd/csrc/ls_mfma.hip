@@ -4,10 +4,11 @@
 // 16 neurons, [16 x d] weight rows times [d x B] activations.  These kernels run them as
 // v_mfma_f32_16x16x32_{f16,bf16}: the weights are the A operand, loaded straight from
 // their rows (one 16-byte load per lane per step), and the activations are the B operand,
-// token columns.  Activations are fp32, so each one enters as the sum of 16-bit parts (a "hi"
-// part and the 16-bit rounding of the remainder, "lo"; in the resident gate/up kernel a third
-// part for bfloat16), with fp32 accumulation in the matrix cores.  Results match the VALU
-// kernels to fp32 rounding (Eq. 1 of the paper, union over tokens as for the VALU path).
+// token columns.  Activations are fp32, so each one enters as the sum of 16-bit parts, with fp32
+// accumulation in the matrix cores: two or three (input_parts) in the resident gate/up kernel
+// and the down projection beside it, a "hi" part and the 16-bit rounding of the remainder, "lo",
+// in the staged gate/up and the ordered down kernel (in bfloat16 these carry 16 bits; the others
+// match the VALU kernels to fp32 rounding).  Eq. 1 of the paper, union over tokens as for the VALU path.
 //
 // Lane layout of v_mfma_f32_16x16x32 (lane l, i < 8 / i < 4):
 //   A[l % 16][8 (l / 16) + i],  B[8 (l / 16) + i][l % 16],  C[4 (l / 16) + i][l % 16].
@@ -128,8 +129,9 @@ __device__ __forceinline__ void lds_barrier_m() {
 // of 40: 21.1 -> 22.8); its error against 64 bits, activations and output together, is below the
 // vector-ALU kernels' at every width measured, two parts' is above it at 512.
 //
-// Measured against the staged kernel below (which keeps rows longer than the registers hold):
-// Mistral-7B shape at B = 4 (105 blocks, 220 MB) 61.7 -> 41.6 us, 13B shape at B = 8 (138
+// Measured against the staged kernel below (which keeps rows longer than the registers hold, and
+// the thresholded gates of keeps_order): Mistral-7B shape with a ReLU gate at B = 4 (105 blocks, 220
+// MB) 61.7 -> 41.6 us, 13B shape at B = 8 (138
 // blocks, 181 MB) 45.0 -> 37.2 us.  From 45 to 180 MB it reads 7.0 TB/s; about 8 us of a launch
 // are the list, the input's conversion and the last sums.
 constexpr int kGuWaves = kSplitSlices;  // slices, at most
@@ -795,7 +797,8 @@ __global__ __launch_bounds__((64 * kDnWaves<P, BP, NT>)) void down_mfma_kernel(
 }
 
 // The batched down projection of thresholded gates (keeps_order below): one workgroup per NT
-// adjacent 16-column tiles of y and part of the list; its waves split that part's entries.  The down piece of a block for one 16-column tile is [blk/8][16][8]:
+// adjacent 16-column tiles of y and part of the list; its waves split that part's entries.  The
+// down piece of a block for one 16-column tile is [blk/8][16][8]:
 // K step s of an entry is the contiguous kilobyte of chunks 64 s .. 64 s + 63, exactly one A
 // fragment, and the pieces of adjacent tiles are adjacent.  A wave loads the activations of
 // a work item once for its NT fragments: every workgroup reads the whole part's activations
@@ -914,8 +917,8 @@ static bool resident_ok(const Shape& s, int B) {
 
 // A thresholded gate turns the last bit of a sum into a neuron kept or dropped, and in a stack a
 // neuron into another block of the next layer's list.  Where such a gate was batched on the
-// matrix cores with two-part activations (whole K steps a block), the sums
-// keep the order and the parts they have always had, so its decisions stay the same.
+// matrix cores with two-part activations (whole K steps a block), the sums keep the order and
+// the parts they have always had, so its decisions stay the same.
 static bool keeps_order(const Shape& s) { return s.act == LS_ACT_SWIGLU_THRESH && s.blk % 32 == 0; }
 
 // Whether gate/up and down run here for B tokens and a list of up to n entries.  Two and three stay on
@@ -1070,8 +1073,8 @@ static void down_mfma_nt(const Shape& s, const LayerDev& L, const int32_t* slot_
 // splits the activations once per 16 columns instead of once per 64, and its 16 waves leave room
 // for one workgroup per compute unit.  Measured at the longest list the call allows: d = 4096,
 // B = 4: 5 MB of weights 7.4 us against 9.0 with four tiles, 22 MB 12.1 / 12.0, 45 MB 15.1 / 15.4;
-// d = 1984, B = 8: 6 MB 9.4 / 10, 17 MB 15.4 / 11.5; d = 5120 (320 tiles, 256 units), B = 2:
-// 71 MB 32 / 18.
+// d = 1984, B = 8: 6 MB 9.4 / 10, 17 MB 15.4 / 11.5; d = 5120 (320 tiles, 256 units; with 2 tokens,
+// which run on the vector ALU now): 71 MB 32 / 18.  (A longer capacity with a short list: not cut, above.)
 static bool down_one_tile(const Shape& s, int B, int n) {
     return s.d / kColTile <= cu_count() && 2.0 * B * n * s.blk * s.d <= 80e6;
 }
